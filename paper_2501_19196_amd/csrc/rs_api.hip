@@ -481,22 +481,22 @@ int rs_bvh_download(const rs_bvh *bvh, uint32_t *codes, int32_t *perm, int32_t *
 }
 
 // Lane of ray r inside its 64-ray packet (the tile layout of rs_render_fwd).
-static int ray_lane(const rs_rays *rays, int tile_shift, int64_t r)
+static int ray_lane(const rs_rays *rays, int tile_shift, int pkt_shift, int64_t r)
 {
-    if (rays->n_views == 0) return int(r % kWave);
+    if (rays->n_views == 0) return int(r & ((1 << pkt_shift) - 1));
     for (int v = 0; v < rays->n_views; ++v) {
         const rs_view &V = rays->views[v];
         const int64_t local = r - V.ray_offset;
         if (local < 0 || local >= int64_t(V.width) * V.height) continue;
         const int64_t y = local / V.width, x = local - y * V.width;
-        const int tw = 1 << tile_shift, th = kWave >> tile_shift;
+        const int tw = 1 << tile_shift, th = 1 << (pkt_shift - tile_shift);
         return int((y % th) * tw + (x % tw));
     }
     return 0;
 }
 
 // Host copies of stored lists (the list bookkeeping of a ray set and its pool).
-static int lists_download(const rs_rays *rays, int tile_shift, const int4 *dev_list, const ListPool &P,
+static int lists_download(const rs_rays *rays, const rs_params *p, const int4 *dev_list, const ListRoom &room,
                           const int64_t *sel, int64_t n_sel, int32_t *count, int32_t *stored, int32_t *extra,
                           int32_t *ids, int32_t cap)
 {
@@ -508,15 +508,19 @@ static int lists_download(const rs_rays *rays, int tile_shift, const int4 *dev_l
             if (sel[i] < 0 || sel[i] >= n) return RS_ERR_INVALID_ARG;
     std::vector<int4> li(static_cast<size_t>(n));
     if (hipMemcpy(li.data(), dev_list, size_t(n) * 16, hipMemcpyDeviceToHost) != hipSuccess) return RS_ERR_HIP;
-    unsigned long long taken = 0;
-    if (hipMemcpy(&taken, P.hdr, 8, hipMemcpyDeviceToHost) != hipSuccess) return RS_ERR_HIP;
+    // the packet size that the forward pass took
+    unsigned long long head[2] = {0, 0};
+    if (hipMemcpy(head, room.base, 16, hipMemcpyDeviceToHost) != hipSuccess) return RS_ERR_HIP;
+    const unsigned long long taken = head[0];
+    const int pkt_shift = (head[1] >> 32) == 4 ? 4 : 6, tile_shift = pkt_shift == 6 ? tile_shift_of(p) : pkt_shift / 2;
+    const ListPool P = list_pool_at(room, chunk_slots_of(pkt_shift));
     const int64_t used = int64_t(taken < (unsigned long long)P.chunks ? taken : (unsigned long long)P.chunks);
     std::vector<int32_t> prev(size_t(used > 0 ? used : 1)), fill(size_t(used > 0 ? used : 1));
-    std::vector<uint32_t> slots(size_t(used > 0 ? used : 1) * kChunkSlots);
+    std::vector<uint32_t> slots(size_t(used > 0 ? used : 1) * size_t(P.chunk_slots));
     if (used > 0) {
         if (hipMemcpy(prev.data(), P.prev, size_t(used) * 4, hipMemcpyDeviceToHost) != hipSuccess ||
             hipMemcpy(fill.data(), P.fill, size_t(used) * 4, hipMemcpyDeviceToHost) != hipSuccess ||
-            hipMemcpy(slots.data(), P.slots, size_t(used) * kChunkSlots * 4, hipMemcpyDeviceToHost) != hipSuccess)
+            hipMemcpy(slots.data(), P.slots, size_t(used) * P.chunk_slots * 4, hipMemcpyDeviceToHost) != hipSuccess)
             return RS_ERR_HIP;
     }
     // a packet's rows, first to last: (first slot, lane mask); a chunk's rows are found
@@ -535,20 +539,20 @@ static int lists_download(const rs_rays *rays, int tile_shift, const int4 *dev_l
                 int64_t hops = 0;
                 for (int32_t c = L.z; c >= 0 && c < used && hops <= used; c = prev[size_t(c)], ++hops) {
                     int32_t end = fill[size_t(c)];
-                    if (end < 0 || end > kChunkSlots) break;
+                    if (end < 0 || end > P.chunk_slots) break;
                     while (end >= 2) {
-                        const size_t at = size_t(c) * kChunkSlots + size_t(end);
+                        const size_t at = size_t(c) * P.chunk_slots + size_t(end);
                         const uint64_t mask = uint64_t(slots[at - 2]) | (uint64_t(slots[at - 1]) << 32);
                         const int32_t k = __builtin_popcountll(mask);
                         if (k + 2 > end) break;
                         end -= k + 2;
-                        rows.emplace_back(int64_t(c) * kChunkSlots + end, mask);
+                        rows.emplace_back(int64_t(c) * P.chunk_slots + end, mask);
                     }
                 }
                 std::reverse(rows.begin(), rows.end());
                 it = chains.emplace(L.z, std::move(rows)).first;
             }
-            const int lane = ray_lane(rays, tile_shift, r);
+            const int lane = ray_lane(rays, tile_shift, pkt_shift, r);
             for (const auto &row : it->second) {
                 if (!((row.second >> lane) & 1ull)) continue;
                 const uint64_t below = lane ? row.second & ((1ull << lane) - 1ull) : 0ull;
@@ -578,8 +582,8 @@ int rs_hit_lists_download(const rs_rays *rays, const rs_params *p, const void *r
     if (rays->n == 0) return RS_OK;
     const StateLayout SL = state_layout(rays->n, p->hit_list);
     char *base = const_cast<char *>(static_cast<const char *>(ray_state));
-    return lists_download(rays, tile_shift_of(p), reinterpret_cast<const int4 *>(base + SL.list),
-                          list_pool_at(base + SL.pool, SL.chunks), rays_sel, n_sel, count, stored, extra, ids, cap);
+    return lists_download(rays, p, reinterpret_cast<const int4 *>(base + SL.list), ListRoom{base + SL.pool, SL.chunks},
+                          rays_sel, n_sel, count, stored, extra, ids, cap);
 }
 
 int rs_mesh_hit_lists_download(const rs_rays *rays, const rs_params *p, const rs_shading *sh, const void *frame,
@@ -595,11 +599,11 @@ int rs_mesh_hit_lists_download(const rs_rays *rays, const rs_params *p, const rs
     if (hipStreamSynchronize(static_cast<hipStream_t>(stream)) != hipSuccess) return RS_ERR_HIP;
     if (rays->n == 0) return RS_OK;
     SetState st;
-    ListPool pool;
+    ListRoom pool;
     if ((e = mesh_frame_set(const_cast<char *>(static_cast<const char *>(frame)), rays->n, p->hit_list,
                             sh->max_bounces, set, &st, &pool)))
         return e;
-    return lists_download(rays, tile_shift_of(p), st.list, pool, rays_sel, n_sel, count, stored, nullptr, ids, cap);
+    return lists_download(rays, p, st.list, pool, rays_sel, n_sel, count, stored, nullptr, ids, cap);
 }
 
 }  // extern "C"

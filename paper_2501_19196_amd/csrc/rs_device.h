@@ -20,15 +20,17 @@ constexpr float kInf = __builtin_huge_valf();
 
 // --------------------------------------------------------------- packets
 
-// Host: fill the view table of a launch (tiles of 2^tile_shift x 64 / 2^tile_shift
-// pixels) and return its packet count.
+// Host: fill the view table of a launch (packets of 2^pkt_shift rays, in views tiles of
+// 2^tile_shift x 2^(pkt_shift - tile_shift) pixels) and return its packet count.
 template <typename PT>
-inline int64_t plan_packets(PT &P, const rs_rays *rays, int tile_shift)
+inline int64_t plan_packets(PT &P, const rs_rays *rays, int tile_shift, int pkt_shift)
 {
     P.n_views = rays->n_views;
     P.tile_shift = tile_shift;
-    if (rays->n_views == 0) return (rays->n + kWave - 1) / kWave;
-    const int tw = 1 << tile_shift, th = kWave >> tile_shift;
+    P.pkt_shift = pkt_shift;
+    const int64_t lanes = int64_t(1) << pkt_shift;
+    if (rays->n_views == 0) return (rays->n + lanes - 1) / lanes;
+    const int tw = 1 << tile_shift, th = 1 << (pkt_shift - tile_shift);
     int64_t packets = 0;
     for (int v = 0; v < rays->n_views; ++v) {
         const rs_view &V = rays->views[v];
@@ -69,9 +71,10 @@ __device__ inline int64_t strip_major_packet(const PT &P, int64_t pkt, int strip
 template <typename PT>
 __device__ inline int64_t packet_ray(const PT &P, int64_t pkt, int lane, bool &valid)
 {
+    const int ps = P.pkt_shift;
     if (P.n_views == 0) {
-        int64_t r = pkt * kWave + lane;
-        valid = r < P.n_rays;
+        int64_t r = (pkt << ps) + lane;
+        valid = r < P.n_rays && (lane >> ps) == 0;
         return r;
     }
     int v = 0;
@@ -82,8 +85,8 @@ __device__ inline int64_t packet_ray(const PT &P, int64_t pkt, int lane, bool &v
     int64_t local = pkt - V.first_packet;
     int64_t ty = local / V.tiles_x, tx = local - ty * V.tiles_x;
     int64_t x = (tx << sh) + (lane & ((1 << sh) - 1));
-    int64_t y = ty * (kWave >> sh) + (lane >> sh);
-    valid = x < V.width && y < V.height;
+    int64_t y = (ty << (ps - sh)) + (lane >> sh);
+    valid = x < V.width && y < V.height && (lane >> ps) == 0;
     return V.ray_offset + y * V.width + x;
 }
 

@@ -25,6 +25,30 @@ inline int tile_shift_of(const rs_params *p)
     default: return 3;
     }
 }
+// log2 of the rays per packet of a launch over `sets` ray sets. A launch needs some thousands of packets to
+// fill the chip, and the rays of a small image lie far apart, so a 64-ray packet of one spans a wide
+// bundle: launches of few rays, and those over small views of large scenes, trace 16-ray packets.
+// Forward and adjoint, 16-ray against 64-ray packets: 3000 Gaussians, 77k rays 0.30 and 0.33 ms, 128k rays
+// 0.40 and 0.33; 300k, 480x320 2.6 and 4.1; 500k, 640x480 4.9 and 4.2; 1M, 480x320 7.4 and 13.6, 640x480 8.1
+// and 8.1; 260k, three views of 406x228 and four of 203x85 6.3 and 12.9. The paper variant keeps 64: its
+// pool bound counts on full rows.
+constexpr int64_t kSmallLaunchRays = 98304, kMidLaunchRays = 524288, kSmallViewRays = 196608;
+inline int packet_shift(const rs_rays *rays, int64_t sets, const rs_params *p, int64_t n_gauss)
+{
+    if (p && (p->flags & RS_PAPER_GRADIENT)) return 6;
+    const int64_t n = rays->n * sets, per_view = rays->n / (rays->n_views > 0 ? rays->n_views : 1);
+    const bool small_views = n <= kMidLaunchRays && per_view <= kSmallViewRays && n_gauss >= per_view;
+    return n <= kSmallLaunchRays || small_views ? 4 : 6;
+}
+// The same for a pass that neither writes nor reads stored lists (whose rows name lanes of the
+// packets that wrote them): where the Gaussians far outnumber the rays, even 16-ray packets are wide,
+// and 4-ray ones are faster (1M Gaussians, 320x180: 2.7 against 4.4 ms; 200k Gaussians, 400x300: 3.9
+// against 1.2).
+inline int packet_shift_no_lists(const rs_rays *rays, int64_t sets, const rs_params *p, int64_t n_gauss)
+{
+    const int ps = packet_shift(rays, sets, p, n_gauss);
+    return ps == 4 && n_gauss >= 4 * rays->n * sets ? 2 : ps;
+}
 constexpr int kSortBlock = 256;
 constexpr int kSortItems = 8;  // keys per thread per sort tile
 constexpr int kSortTile = kSortBlock * kSortItems;
@@ -190,19 +214,21 @@ struct SetState {
 // consumed a hit at that step, in lane order (the Gaussian index it composited,
 // or the index | kListSecond for a hit it only collected in the paper variant's
 // second phase), then the 64-bit mask of those lanes as two words. Rows are
-// packed into chunks of kChunkSlots 4-byte slots (a row never straddles two
+// packed into chunks of 4-byte slots (8 per ray of a packet; a row never straddles two
 // chunks), linked backwards per packet; fill[c] is the number of slots chunk c
 // holds. The pool header holds the chunk counter (64-bit) and a flag set when a
 // packet found the pool exhausted (its later rows are not stored).
-constexpr int kChunkSlots = 512;
+constexpr int kChunkSlots = 512;  // the unit in which pools are sized, and a chunk of 64-ray packets
+inline int chunk_slots_of(int pkt_shift) { return kChunkSlots >> (6 - pkt_shift); }
 constexpr uint32_t kListIdle = 0xffffffffu;
 constexpr uint32_t kListSecond = 0x80000000u;
 struct ListPool {
-    unsigned long long *hdr;  // [0] chunks taken, [1] exhausted flag
+    unsigned long long *hdr;  // [0] chunks taken, [1] exhausted flag; its upper half: log2 of the rays per packet
     int32_t *prev;            // [chunks] previous chunk of the same packet (-1: first)
     int32_t *fill;            // [chunks] slots used
-    uint32_t *slots;          // [chunks][kChunkSlots]
+    uint32_t *slots;          // [chunks][chunk_slots]
     int64_t chunks;
+    int32_t chunk_slots;
 };
 inline int64_t list_chunks(int64_t slots_wanted)
 {
@@ -214,15 +240,32 @@ inline size_t list_pool_bytes(int64_t chunks)
     if (chunks <= 0) return 0;
     return 256 + 2 * align256(size_t(chunks) * 4) + size_t(chunks) * kChunkSlots * 4;
 }
-inline ListPool list_pool_at(char *base, int64_t chunks)
+// Where a pool lies: the bytes of `units` chunks of kChunkSlots slots (list_pool_bytes). The launch carves them,
+// since the packet size depends on the scene too.
+struct ListRoom {
+    char *base;
+    int64_t units;
+};
+// The pool in the bytes of `units` chunks of kChunkSlots slots. Smaller chunks have more links and
+// fills: as many chunks as then fit.
+inline ListPool list_pool_at(const ListRoom &at, int chunk_slots)
 {
-    ListPool P{nullptr, nullptr, nullptr, nullptr, 0};
-    if (!base || chunks <= 0) return P;
+    char *base = at.base;
+    const int64_t units = at.units;
+    ListPool P{};
+    if (!base || units <= 0) return P;
+    const size_t room = list_pool_bytes(units) - 256;
+    int64_t chunks = units;
+    if (chunk_slots != kChunkSlots) {
+        chunks = int64_t(room / (size_t(chunk_slots) * 4 + 8));
+        while (2 * align256(size_t(chunks) * 4) + size_t(chunks) * chunk_slots * 4 > room) --chunks;
+    }
     P.hdr = reinterpret_cast<unsigned long long *>(base);
     P.prev = reinterpret_cast<int32_t *>(base + 256);
     P.fill = reinterpret_cast<int32_t *>(base + 256 + align256(size_t(chunks) * 4));
     P.slots = reinterpret_cast<uint32_t *>(base + 256 + 2 * align256(size_t(chunks) * 4));
     P.chunks = chunks;
+    P.chunk_slots = chunk_slots;
     return P;
 }
 
@@ -273,9 +316,9 @@ enum class Pass { Forward, AdjointList, AdjointTraverse };
 
 int launch_build(const rs_gaussians *g, float Q, bool lbvh, char *ws, hipStream_t st);
 int launch_sets(const BvhDesc &D, const rs_gaussians *g, const rs_params *p, int nsets, const SetDesc *sets,
-                const ListPool &pool, Pass pass, hipStream_t st);
+                const ListRoom &room, Pass pass, hipStream_t st);
 // zero a pool's header (before a forward that stores lists)
-void reset_pool(const ListPool &pool, hipStream_t st);
+void reset_pool(const ListPool &pool, int pkt_shift, hipStream_t st);
 int launch_render(const BvhDesc &D, const rs_gaussians *g, const rs_rays *rays, const rs_params *p, float *out_rgb,
                   void *state, const float *grad, const rs_grads *grads, hipStream_t st);
 void zero_gacc(const BvhDesc &D, hipStream_t st);
@@ -283,7 +326,7 @@ int launch_build_mesh(const rs_mesh *m, char *ws, hipStream_t st);
 int launch_trace_mesh(const BvhDesc &M, const rs_rays *rays, const float *t_limit, int any_hit, int tile_shift, float *t_hit,
                       int32_t *tri, hipStream_t st);
 size_t mesh_frame_bytes(int64_t n, int32_t cap, int bounces);
-int mesh_frame_set(char *frame, int64_t n, int32_t cap, int bounces, int set, SetState *st, ListPool *pool);
+int mesh_frame_set(char *frame, int64_t n, int32_t cap, int bounces, int set, SetState *st, ListRoom *room);
 size_t loss_workspace_bytes(int32_t w, int32_t h);
 int launch_loss(const float *img, const float *tgt, int32_t w, int32_t h, const rs_loss_params *lp, float *loss,
                 float *grad, void *ws, hipStream_t st);

@@ -19,7 +19,7 @@ struct MeshParams {
     int32_t root;
     int32_t any_hit;
     int32_t n_views;
-    int32_t tile_shift;
+    int32_t tile_shift, pkt_shift;
     ViewEntry views[RS_MAX_VIEWS];
 };
 
@@ -171,7 +171,7 @@ struct ShadowLevel {
 struct Frame {
     PathLevel P[RS_MAX_BOUNCES + 1];
     ShadowLevel S[RS_MAX_BOUNCES];
-    ListPool pool;
+    ListRoom pool;
     int32_t bounces;
     size_t total;
 };
@@ -225,9 +225,8 @@ static Frame frame_layout(char *base, int64_t n, int32_t cap, int bounces)
         S.g = fl(3);
     }
     if (cap > 0 && n > 0) {
-        const int64_t chunks = list_chunks(n * int64_t(cap) * (2 * bounces + 1));
-        F.pool = list_pool_at(take(list_pool_bytes(chunks)), chunks);
-        if (!base) F.pool.chunks = chunks;
+        const int64_t units = list_chunks(n * int64_t(cap) * (2 * bounces + 1));
+        F.pool = ListRoom{take(list_pool_bytes(units)), units};
     }
     F.total = off;
     return F;
@@ -440,7 +439,7 @@ static MeshParams mesh_params(const BvhDesc &M, const rs_rays *rays, int any_hit
     P.root = M.root;
     P.n_tris = M.n;
     P.any_hit = any_hit;
-    P.n_packets = plan_packets(P, rays, tile_shift);
+    P.n_packets = plan_packets(P, rays, tile_shift, 6);
     return P;
 }
 
@@ -460,12 +459,12 @@ int launch_trace_mesh(const BvhDesc &M, const rs_rays *rays, const float *t_limi
 size_t mesh_frame_bytes(int64_t n, int32_t cap, int bounces) { return frame_layout(nullptr, n, cap, bounces).total; }
 
 // The state and list pool of ray set `set` of a frame (0..B: path levels, B+1..2B: shadow levels).
-int mesh_frame_set(char *frame, int64_t n, int32_t cap, int bounces, int set, SetState *st, ListPool *pool)
+int mesh_frame_set(char *frame, int64_t n, int32_t cap, int bounces, int set, SetState *st, ListRoom *room)
 {
     if (set < 0 || set > 2 * bounces) return RS_ERR_INVALID_ARG;
     const Frame F = frame_layout(frame, n, cap, bounces);
     *st = set <= bounces ? F.P[set].st : F.S[set - bounces - 1].st;
-    *pool = F.pool;
+    *room = F.pool;
     return RS_OK;
 }
 
@@ -583,7 +582,7 @@ int launch_mesh_bwd(const BvhDesc &G, const rs_gaussians *g, const rs_shading *s
         rs_params ps = *p;
         ps.flags |= RS_PERSISTENT;
         int e;
-        if (F.pool.chunks > 0) {
+        if (F.pool.units > 0) {
             // stored lists of all sets, then traversal for the rays whose list is incomplete
             if ((e = launch_sets(G, g, &ps, nsets, S, F.pool, Pass::AdjointList, st))) return e;
         }

@@ -47,9 +47,10 @@ struct RenderParams {
     uint32_t flags;
     int32_t persistent;
     int32_t brute;
+    int32_t front;         // forward: the frontier kernel (else the depth-first walk)
     int32_t count;
     int32_t n_views;
-    int32_t tile_shift;
+    int32_t tile_shift, pkt_shift;
     int32_t strip_tiles;   // persistent: tile strip width of the packet order (0 = row-major)
     int32_t lists;         // stored hit lists: the forward appends rows, the adjoint replays them
     int32_t overflow_only; // traversal adjoint next to stored lists: only rays whose list is incomplete
@@ -151,6 +152,10 @@ __device__ inline float hit_key_t(double k)
 }
 __device__ inline uint32_t hit_key_gid(double k) { return uint32_t(uint64_t(__double_as_longlong(k))); }
 
+// The smallest key of depth t >= 0 (any real key with t1 < t lies below it, any other above or at it;
+// a key of t1 = +inf or NaN lies above it for t = +inf, one of a negative t1 below every such key).
+__device__ inline double bound_key(float t) { return hit_key(t, 0u); }
+
 // Sorted insert of k into the ascending keys key[0..N): slot s becomes max(key[s-1],
 // min(key[s], k)) and slot 0 min(key[0], k), each from the old keys, so the 2N operations do
 // not form a chain through a carried key. They are issued from the back, each max three slots
@@ -199,6 +204,8 @@ struct HitBuf {
     // are never NaN, so the min/max are the bare instructions: the generic fmin/fmax would first
     // quiet every loop-carried key (one more v_max_f64 per entry in IEEE mode).
     __device__ inline void insert(double k) { sorted_insert<K, false>(key, k); }
+    // the same, returning the key that falls off (kNoHit: none)
+    __device__ inline double insert_out(double k) { return sorted_insert<K, true>(key, k); }
 };
 
 // The same sorted buffer of KR + KT keys with its last KT entries in LDS: a per-wave ring of KT
@@ -521,25 +528,6 @@ __device__ inline void recompute_hit(bool act, uint32_t gid, const Ray &ray, con
     }
 }
 
-// (js: the hit's sorted position, looked up by the caller ahead of time)
-__device__ inline void composite_hit(bool act, uint32_t gid, int32_t js, const Ray &ray,
-                                     const float4 *__restrict__ records, const float *__restrict__ rgb, bool zc,
-                                     const RenderParams &P, Accum &A, HitData &H)
-{
-    H.al = H.cr = H.cg = H.cb = H.t1 = H.h2 = 0.0f;
-    H.g = HitGeom{};
-    if (act) {
-        H.al = hit_alpha_at(js, ray, records, P.Q, H.r0, H.r1, H.r2, H.r3, H.t1, H.h2, H.g);
-        if (!zc) {
-            H.cr = rgb[3 * gid];
-            H.cg = rgb[3 * gid + 1];
-            H.cb = rgb[3 * gid + 2];
-        }
-    }
-    H.Tk = A.T;
-    if (act) composite_step(A, H.al, H.cr, H.cg, H.cb);
-}
-
 // ------------------------------------------------------- back-to-front adjoint
 
 // Smallest normal float: below it T loses relative precision, so the adjoint does not
@@ -801,6 +789,7 @@ struct ListCursor {
     int32_t chunk;  // current chunk (-1: none yet)
     int32_t fill;   // slots used in the current chunk
     int32_t slots;  // slots stored (rows and masks)
+    int32_t first;  // first chunk (-1: none yet)
     bool ok;        // false once the pool was found exhausted
 };
 
@@ -810,20 +799,25 @@ struct ListCursor {
 // and linked to the packet's previous chunk. Once the pool is exhausted the packet
 // stores nothing more (the adjoint then traverses for its rays, or, for the paper
 // variant, the sticky status reports it).
-__device__ inline void list_append(const ListPool &pool, ListCursor &L, uint32_t entry, int lane, int32_t &stored,
-                                   bool paper, int32_t *status)
+// Ends a block that only some lanes run, before wave-uniform values meet again: without it the
+// compiler folds the block's end into the next join, takes that join's values for divergent and
+// keeps them, and every branch on them, per lane.
+__device__ inline void rejoin() { __builtin_amdgcn_wave_barrier(); }
+
+__device__ inline void list_append(const ListPool &pool, ListCursor &L, uint32_t entry, int lane, bool paper,
+                                   int32_t *status)
 {
-    if (!L.ok) return;
     const uint64_t m = wave_ballot(entry != kListIdle);
     if (m == 0) return;
     const int32_t need = __popcll(m) + 2;
-    if (L.chunk < 0 || L.fill + need > kChunkSlots) {
+    if (L.chunk < 0 || L.fill + need > pool.chunk_slots) {
         int32_t c = 0;
         if (lane == 0) {
             if (L.chunk >= 0) pool.fill[L.chunk] = L.fill;
             const unsigned long long k = atomicAdd(pool.hdr, 1ull);
             c = k < (unsigned long long)pool.chunks ? int32_t(k) : -1;
         }
+        rejoin();
         c = __builtin_amdgcn_readfirstlane(c);
         if (c < 0) {
             L.ok = false;
@@ -831,24 +825,27 @@ __device__ inline void list_append(const ListPool &pool, ListCursor &L, uint32_t
                 atomicOr(pool.hdr + 1, 1ull);
                 if (paper) atomicOr(status, kStatusListPool);
             }
+            rejoin();
             return;
         }
         if (lane == 0) pool.prev[c] = L.chunk;
+        rejoin();
+        if (L.chunk < 0) L.first = c;
         L.chunk = c;
         L.fill = 0;
     }
     // The rows are streamed out with nontemporal stores: they are read back only by the adjoint,
     // after this launch, and the forward's own fetches wait less behind them.
-    uint32_t *row = pool.slots + int64_t(L.chunk) * kChunkSlots + L.fill;
+    uint32_t *row = pool.slots + int64_t(L.chunk) * pool.chunk_slots + L.fill;
     if (entry != kListIdle) {
         const uint32_t below = __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
         __builtin_nontemporal_store(entry, row + below);
-        if (entry < kListSecond) ++stored;
     }
     if (lane == 0) {
         __builtin_nontemporal_store(uint32_t(m), row + need - 2);
         __builtin_nontemporal_store(uint32_t(m >> 32), row + need - 1);
     }
+    rejoin();
     L.fill += need;
     L.slots += need;
     ++L.rows;
@@ -1006,208 +1003,1004 @@ constexpr int waves_for(int K, bool bwd)
 
 // ------------------------------------------------------------ forward render
 
+// A lane's ray while its packet is traced: the front-to-back accumulator, and with
+// RS_PAPER_GRADIENT its second phase: after an eps1 stop the lane keeps consuming hits without
+// compositing them, recording their ids while T2 (their transmittance) stays >= eps2.
+struct LaneState {
+    Ray ray;
+    Accum A;
+    bool live;
+    double last;  // the last consumed key
+    bool phase2;
+    float T2;
+    int32_t extra;
+};
+
+// What a lane seldom writes lives in LDS: T just before the composited hit that took T below the
+// normal floats (to 0, or into the subnormals, where T_{k+1} / (1 - alpha_k) would lose its digits)
+// and that hit's index, and how many composited ids were stored when the list pool ran out.
+struct LaneCold {
+    float Tz[kWave];
+    int32_t z[kWave], stored[kWave];
+};
+
+__device__ inline void lane_reset(LaneState &S, LaneCold &C, bool live, int lane)
+{
+    S.A = Accum{1.0f, 0.0f, 0.0f, 0.0f, 0};
+    S.live = live;
+    S.last = -kNoHit;
+    S.phase2 = false;
+    S.T2 = 1.0f;
+    S.extra = 0;
+    C.Tz[lane] = 0.0f;
+    C.z[lane] = -1;
+}
+
+// One compositing step of the wave: the lanes with `act` consume their hit `key`, of opacity al and
+// colour c.
+template <bool PAPER>
+__device__ inline void consume_known(bool act, double key, float al, float cr, float cg, float cb, LaneState &S,
+                                     LaneCold &C, const Ptrs &ptr, const RenderParams &P, bool lists, ListCursor &LC,
+                                     int lane)
+{
+    const bool paper = PAPER && P.paper && lists;
+    const uint32_t gid = hit_key_gid(key);
+    uint32_t entry = kListIdle;
+    if (paper && S.phase2) {
+        if (act) {
+            if (S.T2 < P.eps2 || S.A.n + S.extra >= P.max_hits) {
+                S.live = false;  // the second phase ends before this hit
+            } else {
+                entry = gid | kListSecond;
+                S.T2 *= 1.0f - al;
+                ++S.extra;
+                S.last = key;
+            }
+        }
+    } else {
+        const float Tk = S.A.T;
+        if (act) {
+            composite_step(S.A, al, cr, cg, cb);
+            entry = gid;
+            S.last = key;
+            if (S.A.T < kMinNormal && Tk >= kMinNormal) {
+                C.Tz[lane] = Tk;
+                C.z[lane] = S.A.n - 1;
+            }
+        }
+        const bool stopped = act && stop_after(S.A, P);
+        if (stopped) {
+            if (paper && S.A.T < P.eps1)
+                S.phase2 = true;  // stays live for the second phase
+            else
+                S.live = false;
+        }
+        rejoin();
+    }
+    if (lists && LC.ok) {
+        list_append(ptr.pool, LC, entry, lane, paper, ptr.status);
+        if (!LC.ok) C.stored[lane] = S.A.n - (entry < kListSecond ? 1 : 0);
+    }
+    rejoin();
+}
+
+// The same with the hit's opacity and colour fetched here (Gaussian at sorted position js): alpha is
+// recomputed from the record with the leaf test's own arithmetic.
+template <bool PAPER>
+__device__ inline void consume(bool act, double key, int32_t js, LaneState &S, LaneCold &C,
+                               const float4 *__restrict__ records, const Ptrs &ptr, const RenderParams &P, bool zc,
+                               bool lists, ListCursor &LC, int lane)
+{
+    float al = 0.0f, cr = 0.0f, cg = 0.0f, cb = 0.0f;
+    if (act) {
+        float4 r0, r1, r2, r3;
+        float t1, h2;
+        HitGeom hg;
+        al = hit_alpha_at(js, S.ray, records, P.Q, r0, r1, r2, r3, t1, h2, hg);
+        if (!zc) {
+            const uint32_t gid = hit_key_gid(key);
+            cr = ptr.rgb[3 * int64_t(gid)];
+            cg = ptr.rgb[3 * int64_t(gid) + 1];
+            cb = ptr.rgb[3 * int64_t(gid) + 2];
+        }
+    }
+    rejoin();
+    consume_known<PAPER>(act, key, al, cr, cg, cb, S, C, ptr, P, lists, LC, lane);
+}
+
+// The outputs and the adjoint's starting state of a packet's rays.
+__device__ inline void write_rays(const LaneState &S, const LaneCold &C, const LaneRay &LR, const RaySet &R,
+                                  const Ptrs &ptr, const ListCursor &LC, bool lists, int lane)
+{
+    if (lists) list_close(ptr.pool, LC, lane);
+    if (!LR.valid) return;
+    const float orr = __builtin_fmaf(S.A.T, LR.bgr, S.A.Cr), og = __builtin_fmaf(S.A.T, LR.bgg, S.A.Cg),
+                ob = __builtin_fmaf(S.A.T, LR.bgb, S.A.Cb);
+    R.out_rgb[3 * LR.id] = orr;
+    R.out_rgb[3 * LR.id + 1] = og;
+    R.out_rgb[3 * LR.id + 2] = ob;
+    if (R.fin) {
+        R.fin[LR.id] = make_float4(orr, og, ob, S.A.T);
+        const uint64_t kb = S.A.n > 0 ? uint64_t(__double_as_longlong(S.last)) : 0ull;
+        const int32_t z = C.z[lane];
+        R.last[LR.id] = make_uint4(uint32_t(kb), uint32_t(kb >> 32), __float_as_uint(C.Tz[lane]),
+                                   z >= 0 ? uint32_t(S.A.n - 1 - z) : 0xffffffffu);
+    }
+    if (lists) R.list[LR.id] = make_int4(S.A.n, LC.ok ? S.A.n : C.stored[lane], LC.chunk, LC.rows);
+}
+
+// Work counters of a forward wave (wave-uniform; only in the COUNT variants).
+struct FwdCount {
+    uint64_t pkt, node, leaf, round, lleaf, lbuf, lcomp, lchild, rows, slots;
+};
+__device__ inline void add_counts(const FwdCount &c, const Ptrs &ptr, int lane)
+{
+    if (lane != 0 || c.pkt == 0) return;
+    atomicAdd(ptr.counters + 0, (unsigned long long)c.pkt);
+    atomicAdd(ptr.counters + 1, (unsigned long long)c.node);
+    atomicAdd(ptr.counters + 2, (unsigned long long)c.leaf);
+    atomicAdd(ptr.counters + 3, (unsigned long long)c.round);
+    atomicAdd(ptr.counters + 4, (unsigned long long)c.lleaf);
+    atomicAdd(ptr.counters + 5, (unsigned long long)c.lbuf);
+    atomicAdd(ptr.counters + 6, (unsigned long long)c.lcomp);
+    atomicAdd(ptr.counters + 7, (unsigned long long)c.lchild);
+    atomicAdd(ptr.counters + 12, (unsigned long long)c.rows);
+    atomicAdd(ptr.counters + 14, (unsigned long long)c.slots);
+}
+
+// The depth-first walk of a packet, in rounds, until no lane is live. OCTS: specialised on the
+// direction octant (else one generic form, where the walk is the exception). Returns false when
+// the traversal stack overflowed.
+template <typename BUF, bool BRUTE, bool OCTS, bool COUNT, bool PAPER>
+__device__ inline bool walk_rounds(LaneState &S, LaneCold &C, const LaneRay &LR, bool zc, bool lists, ListCursor &LC,
+                                   const float4 *__restrict__ records, const float4 *__restrict__ nodes,
+                                   const int32_t *__restrict__ gidx, const int32_t *__restrict__ inv, const Ptrs &ptr,
+                                   const RenderParams &P, BUF &hb, int lane, FwdCount &cnt)
+{
+    constexpr bool kRev = false;
+    const Ray &ray = S.ray;
+    const float tmax = LR.tmax;
+    bool &live = S.live;
+    const Slab sl = make_slab(ray);
+    const int oct = OCTS ? wave_octant(sl, LR.valid) : kMixedOctant;
+    bool overflow = false;
+    uint64_t c_node = 0, c_lchild = 0;
+    while (wave_ballot(live)) {
+        hb.clear();
+        if (COUNT) ++cnt.round;
+        const double last = S.last;
+        // NaN on lanes that are not live: no box test passes for them
+        const float t_lo =
+            !live ? __builtin_nanf("") : (last == -kNoHit ? P.t_min : fmaxf(P.t_min, hit_key_t(last)));
+        float t_hi_w = widen(tmax, sl.pad);
+
+        // the round's live lanes as a mask: the leaf step combines per-compare masks with it
+        // (a ballot of a compound condition would first turn it into a vector value)
+        const uint64_t live_now = wave_ballot(live);
+        auto leaf = [&](int64_t j) {
+            const int64_t js = __builtin_amdgcn_readfirstlane(int32_t(j));
+            const float4 r0 = records[4 * js + 0], r1 = records[4 * js + 1], r2 = records[4 * js + 2],
+                         r3 = records[4 * js + 3];
+            const uint32_t gid = uint32_t(gidx[js]);
+            // every lane evaluates the test and the key (no divergent branch); only lanes
+            // whose ray hits take part, and the entry distance and key only when one does
+            HitGeom hg;
+            const float h2 = ellipsoid_h2(ray, r0, r1, r2, r3, hg);
+            // the index load is issued with the record's (its latency hides behind theirs)
+            asm volatile("" ::"s"(gid));
+            if (COUNT) {
+                ++cnt.leaf;
+                cnt.lleaf += __popcll(live_now);
+            }
+            const uint64_t hmask = wave_ballot(h2 <= P.Q) & live_now;
+            if (!hmask) return;
+            const float t1 = ellipsoid_t1(hg, r2, h2, P.Q);
+            const double k = hit_key(t1, gid);
+            const uint64_t cmask = hmask & wave_ballot(t1 >= P.t_min) & wave_ballot(t1 < tmax) &
+                                   wave_ballot(k > last) & wave_ballot(k < hb.last());
+            const bool cand = __builtin_amdgcn_inverse_ballot_w64(cmask);
+            if (COUNT) cnt.lbuf += __popcll(cmask);
+            if (cmask) {
+                // every lane runs the insertion network; lanes without a candidate insert
+                // the empty key, which moves nothing
+                hb.insert(cand ? k : kNoHit);
+                if (hb.last() != kNoHit) t_hi_w = widen(fminf(tmax, hit_key_t(hb.last())), sl.pad);
+            }
+        };
+
+        if (BRUTE) {
+            for (int64_t j = 0; j < P.n_gauss; ++j) leaf(j);
+        } else if (OCTS) {
+            // While-while traversal: descend internal nodes until a leaf is reached (or the
+            // stack runs dry), then test that leaf; the hit buffer changes only in the leaf step.
+            RS_WALK_BVH()
+        } else {
+            RS_WALK_OCT(kMixedOctant)
+        }
+        if (overflow) {
+            live = false;
+            return false;
+        }
+
+        // composite this round's hits front to back; the buffer is consumed from its front
+        const double round_last = hb.last();
+        bool more = true;
+        // the sorted position of the buffer's front key is looked up one step ahead, so its
+        // latency overlaps the previous step (an empty key reads position 0, unused)
+        int32_t js_next = inv[hb.front() != kNoHit ? hit_key_gid(hb.front()) : 0u];
+#pragma unroll 1
+        for (int s = 0; s < hb.size; ++s) {
+            const double key_s = hb.front();
+            const int32_t js_s = js_next;
+            hb.pop_front();
+            js_next = inv[hb.front() != kNoHit ? hit_key_gid(hb.front()) : 0u];
+            const bool act = more && live && key_s != kNoHit;
+            const uint64_t act_mask = wave_ballot(act);
+            more = act_mask != 0;
+            if (!more) break;
+            if (COUNT) cnt.lcomp += __popcll(act_mask);
+            consume<PAPER>(act, key_s, js_s, S, C, records, ptr, P, zc, lists, LC, lane);
+        }
+        // a lane whose buffer did not fill has consumed all its hits
+        if (live && round_last == kNoHit) live = false;
+    }
+    if (COUNT) {
+        cnt.node += c_node;
+        cnt.lchild += c_lchild;
+    }
+    return true;
+}
+
+// The walk as a kernel of its own: for brute force and for calls that bound the traversal stack.
 template <int K, bool BRUTE, bool COUNT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(waves_for(K, false)))) void k_render(
     const float4 *__restrict__ records, const float4 *__restrict__ nodes, const int32_t *__restrict__ gidx,
     const int32_t *__restrict__ inv, const Ptrs ptr, const RenderParams P)
 {
-    constexpr bool kRev = false;
     const int lane = threadIdx.x;
     int64_t iter_pkt = 0;
     const int xcd = xcd_id();
     int qi = 0;
-    // work counters (wave-uniform, scalar registers; only in the COUNT variants)
-    uint64_t c_pkt = 0, c_node = 0, c_leaf = 0, c_round = 0, c_lleaf = 0, c_lbuf = 0, c_lcomp = 0, c_lchild = 0,
-             c_rows = 0, c_slots = 0;
+    FwdCount cnt{};
     for (;;) {
         const int64_t pkt = next_packet(P, ptr.queue, lane, xcd, qi, iter_pkt);
         if (pkt >= P.n_packets) break;
-        if (COUNT) ++c_pkt;
-
+        if (COUNT) ++cnt.pkt;
         const LaneRay LR = lane_ray(P, ptr, pkt, lane);
-        const RaySet &S = ptr.set[LR.si];
-        const bool zc = S.zero_colour != 0;
-        const bool valid = LR.valid;
-        const int64_t ray_id = LR.id;
-        const Ray ray = LR.ray;
-        const float tmax = LR.tmax, bgr = LR.bgr, bgg = LR.bgg, bgb = LR.bgb;
-        const Slab sl = make_slab(ray);
-        const int oct = wave_octant(sl, valid);
+        const RaySet &R = ptr.set[LR.si];
+        const bool zc = R.zero_colour != 0;
+        const bool lists = P.lists && R.list != nullptr;
+        ListCursor LC{0, -1, 0, 0, -1, true};
+        __shared__ LaneCold cold;
+        LaneState S;
+        S.ray = LR.ray;
+        lane_reset(S, cold, LR.valid && P.n_gauss > 0 && LR.tmax > P.t_min, lane);
+        typename FwdBuf<K>::type hb;
+        if constexpr (!std::is_same<typename FwdBuf<K>::type, HitBuf<K>>::value) {
+            __shared__ double ring[kTailKeys * kWave];
+            hb.ring = ring;
+            hb.lane = lane;
+        }
+        if (!walk_rounds<typename FwdBuf<K>::type, BRUTE, true, COUNT, true>(S, cold, LR, zc, lists, LC, records, nodes,
+                                                                             gidx, inv, ptr, P, hb, lane, cnt))
+            if (lane == 0) atomicOr(ptr.status, kStatusStack);
+        write_rays(S, cold, LR, R, ptr, LC, lists, lane);
+        if (COUNT) {
+            cnt.rows += uint64_t(LC.rows);
+            cnt.slots += uint64_t(LC.slots);
+        }
+    }
+    if (COUNT) add_counts(cnt, ptr, lane);
+}
 
-        Accum A{1.0f, 0.0f, 0.0f, 0.0f, 0};
-        bool live = valid && P.n_gauss > 0 && tmax > P.t_min;
-        double last = -kNoHit;  // the last consumed key; keys of the next round must exceed it
-        // T just before the composited hit that took T below the normal floats (to 0, or into the
-        // subnormals, where T_{k+1} / (1 - alpha_k) would lose its digits), and that hit's index
-        float Tz = 0.0f;
-        int32_t z = -1;
-        // stored hit lists: the packet's row cursor; per lane the composited ids stored
-        const bool lists = P.lists && S.list != nullptr;
-        ListCursor LC{0, -1, 0, 0, true};
-        int32_t stored = 0;
-        // RS_PAPER_GRADIENT forward: after an eps1 stop the lane keeps consuming hits without
-        // compositing them, recording their ids while T2 (their transmittance) stays >= eps2
-        const bool paper = P.paper && lists;
-        bool phase2 = false;
-        float T2 = 1.0f;
-        int32_t extra = 0;
-        bool overflow = false;
+// ------------------------------------------------------- frontier forward
+//
+// The depth-first walk visits a node with the whole wave, one dependent 64-byte fetch per visit,
+// tests every leaf that some ray's box interval meets, and starts again from the root for the rays
+// with more hits than the buffer holds. The frontier kernel turns the search round: the lanes test
+// 64 nodes (or 64 leaves) at a time against the bundle of the packet's rays, in windows of depth
+// from near to far, and only the leaves that survive are tested ray by ray, in order of a lower
+// bound of their depth. So a hit that is nearer than every leaf still to come is final: it is
+// composited and leaves the buffer at once, a packet visits each leaf once, and stops where its
+// rays do.
+//
+// Depth is measured along z, the coordinate axis (with a sign) that a packet's rays run along: z0
+// is the smallest origin, and a ray is u = a_u + z m_u, v = a_v + z m_v over z >= 0, so the bundle
+// is bounded by the extremes of a and m (the four planes of a frustum for rays of one origin).
+// A node is dropped when its box misses the bundle; a leaf when its ellipsoid does (its support
+// against the four planes) or when it misses the tube around the bundle's centre line.
+//
+// Correctness does not rest on the order: lower bounds carry a margin, a lane whose buffer
+// overflows remembers the smallest key it lost (`cap`), takes no hit beyond it and is traced
+// again from its last consumed key, and a hit found after a later one was consumed makes the
+// packet start over with the walk. So the result is the walk's bit for bit.
 
-        while (wave_ballot(live)) {
-            typename FwdBuf<K>::type hb;
-            if constexpr (!std::is_same<typename FwdBuf<K>::type, HitBuf<K>>::value) {
-                __shared__ double ring[kTailKeys * kWave];
-                hb.ring = ring;
-                hb.lane = lane;
-            }
-            hb.clear();
-            if (COUNT) ++c_round;
-            // NaN on lanes that are not live: no box test passes for them
-            const float t_lo =
-                !live ? __builtin_nanf("") : (last == -kNoHit ? P.t_min : fmaxf(P.t_min, hit_key_t(last)));
-            float t_hi_w = widen(tmax, sl.pad);
+constexpr int kFrontActive = 256;  // nodes to expand in this window
+constexpr int kFrontNodes = 192;   // nodes beyond this window
+constexpr int kFrontLeaves = 384;  // leaves tested against the bundle, of this window and beyond
+constexpr int kFrontSorted = 192;  // leaves tested ray by ray per window at most
+constexpr int kFrontRaw = 128;     // leaves found, not yet tested
+constexpr int kFrontWindows = 1 << 14, kFrontRounds = 4096;  // windows of a round, rounds of a packet: then the walk
+constexpr float kFrontFirst = 1.0f;     // Gaussians held that the first window is made for (0.5: 5.7, 1.5: 5.3 ms at 1M; 1.5, 1.8 at 100k)
+// Gaussians a bundle may hold, by volume; beyond that the packet is walked. Rays off curved mirrors span
+// most of the scene, and a bundle drops little of it. (500k Gaussians, 4 x 1024x768 with mirrors: 22 ms at
+// 512 to 2048, 144 at 4096, 34 when all is walked; 1M, 320x180 with lists: 9.6, 6.2 and 5.2 ms at 512, 2048
+// and 4096.)
+constexpr float kFrontHeld = 2048.0f;
+constexpr float kFrontBack = 4e-3f;       // of the depth from which a later round tests boxes, relative
+constexpr float kFrontMargin = 1.2e-4f;  // of a depth bound, relative: the rounding of t1 of flat ellipsoids
 
-            // the round's live lanes as a mask: the leaf step combines per-compare masks with it
-            // (a ballot of a compound condition would first turn it into a vector value)
-            const uint64_t live_now = wave_ballot(live);
-            auto leaf = [&](int64_t j) {
-                const int64_t js = __builtin_amdgcn_readfirstlane(int32_t(j));
-                const float4 r0 = records[4 * js + 0], r1 = records[4 * js + 1], r2 = records[4 * js + 2],
-                             r3 = records[4 * js + 3];
-                const uint32_t gid = uint32_t(gidx[js]);
-                // every lane evaluates the test and the key (no divergent branch); only lanes
-                // whose ray hits take part, and the entry distance and key only when one does
-                HitGeom hg;
-                const float h2 = ellipsoid_h2(ray, r0, r1, r2, r3, hg);
-                // the index load is issued with the record's (its latency hides behind theirs)
-                asm volatile("" ::"s"(gid));
-                if (COUNT) {
-                    ++c_leaf;
-                    c_lleaf += __popcll(live_now);
+struct FrontLds {
+    double start[kWave], stop[kWave];  // a lane's keys lie between them in this round, and in all
+    float from[kWave];                 // depth from which hits are left
+    int32_t ar[kFrontActive];
+    float nz[kFrontNodes];
+    int32_t nr[kFrontNodes];
+    float pz[kFrontLeaves];
+    int32_t pr[kFrontLeaves];
+    float sz[kFrontSorted];
+    int32_t sr[kFrontSorted];
+    int32_t raw[kFrontRaw];
+    uint32_t hist[kWave];
+};
+
+// Wave-wide minimum and sums by DPP: row shifts, then broadcasts across the rows of 16 lanes; the
+// last lane holds the result. A lane without a source keeps its own value.
+template <int CTRL, int ROWS>
+__device__ inline float dpp_min(float x)
+{
+    const float y = __int_as_float(
+        __builtin_amdgcn_update_dpp(__float_as_int(x), __float_as_int(x), CTRL, ROWS, 0xF, false));
+    return fminf(x, y);
+}
+__device__ inline float wave_min(float x)
+{
+    x = dpp_min<0x111, 0xF>(x);  // row_shr 1, 2, 4, 8
+    x = dpp_min<0x112, 0xF>(x);
+    x = dpp_min<0x114, 0xF>(x);
+    x = dpp_min<0x118, 0xF>(x);
+    x = dpp_min<0x142, 0xA>(x);  // row_bcast 15 into rows 1 and 3
+    x = dpp_min<0x143, 0xC>(x);  // row_bcast 31 into rows 2 and 3
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), kWave - 1));
+}
+__device__ inline float wave_max(float x) { return -wave_min(-x); }
+
+__device__ inline uint32_t lanes_below(uint64_t m)
+{
+    return __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
+}
+
+// A packet's axes and ray bundle (wave-uniform but for the lane's own ozr, dz).
+struct Bundle {
+    int ax;      // axis of z; u and v are the next two
+    float sg;    // +1: z along the axis, -1: against it
+    float z0;    // smallest origin (in z)
+    float Au0, Au1, Mu0, Mu1, Av0, Av1, Mv0, Mv1;
+    float ru0, ru1, rv0, rv1;  // 1 / M
+    float zfrom, zlo, zhi;  // hits are wanted from zfrom (zlo for boxes) to zhi
+    float pad;       // absolute slack: rounding at the scale of the origins
+};
+
+__device__ inline float pick(int ax, float x, float y, float z) { return ax == 0 ? x : (ax == 1 ? y : z); }
+
+// Bounds of the rays of the lanes with `on`; (ozr, dz): the lane's origin beyond z0 and its direction
+// along z, so z(t) = ozr + t dz.
+__device__ inline void bundle_bounds(Bundle &B, const Ray &ray, bool on, float ozr, float dz)
+{
+    const float iz = 1.0f / dz;
+    const float mu = pick(B.ax, ray.dy, ray.dz, ray.dx) * iz, mv = pick(B.ax, ray.dz, ray.dx, ray.dy) * iz;
+    const float au = pick(B.ax, ray.oy, ray.oz, ray.ox) - ozr * mu, av = pick(B.ax, ray.oz, ray.ox, ray.oy) - ozr * mv;
+    constexpr float s = 4e-6f;
+    auto lo = [&](float x) { const float m = wave_min(on ? x : kInf); return m - s * fabsf(m); };
+    auto hi = [&](float x) { const float m = wave_max(on ? x : -kInf); return m + s * fabsf(m); };
+    B.Mu0 = lo(mu);
+    B.Mu1 = hi(mu);
+    B.Mv0 = lo(mv);
+    B.Mv1 = hi(mv);
+    B.Au0 = lo(au) - B.pad;
+    B.Au1 = hi(au) + B.pad;
+    B.Av0 = lo(av) - B.pad;
+    B.Av1 = hi(av) + B.pad;
+    // a slope of 0 counts as leaving the box (the lower line rising, the upper one falling), so that
+    // its test is that of A alone
+    auto slope = [](float m, float none) { return fabsf(m) > 1e-30f ? m : none; };
+    B.Mu0 = slope(B.Mu0, 1e-30f);
+    B.Mu1 = slope(B.Mu1, -1e-30f);
+    B.Mv0 = slope(B.Mv0, 1e-30f);
+    B.Mv1 = slope(B.Mv1, -1e-30f);
+    B.ru0 = 1.0f / B.Mu0;
+    B.ru1 = 1.0f / B.Mu1;
+    B.rv0 = 1.0f / B.Mv0;
+    B.rv1 = 1.0f / B.Mv1;
+}
+
+// Whether a box meets the bundle: the depths at which the bundle lies inside each pair of its planes,
+// met with [zlo, zhi]. Its depth bound (with margin) in `near`. The bundle's lower line u = A0 + z M0
+// must lie below the box's upper plane, its upper line above the lower plane: each holds from a depth
+// on (the line runs toward the box) or up to one.
+__device__ inline bool box_meets(const Bundle &B, float lx, float ly, float lz, float hx, float hy, float hz, float &near)
+{
+    const float l = pick(B.ax, lx, ly, lz), h = pick(B.ax, hx, hy, hz);
+    const float lu = pick(B.ax, ly, lz, lx), hu = pick(B.ax, hy, hz, hx);
+    const float lv = pick(B.ax, lz, lx, ly), hv = pick(B.ax, hz, hx, hy);
+    const float za = (B.sg > 0.0f ? l : -h) - B.z0, zb = (B.sg > 0.0f ? h : -l) - B.z0;
+    const float qu0 = (hu - B.Au0) * B.ru0, qu1 = (lu - B.Au1) * B.ru1;
+    const float qv0 = (hv - B.Av0) * B.rv0, qv1 = (lv - B.Av1) * B.rv1;
+    float enter = fmaxf(fmaxf(za, 0.0f), B.Mu0 < 0.0f ? qu0 : 0.0f);
+    enter = fmaxf(fmaxf(enter, B.Mu1 > 0.0f ? qu1 : 0.0f), fmaxf(B.Mv0 < 0.0f ? qv0 : 0.0f, B.Mv1 > 0.0f ? qv1 : 0.0f));
+    float exit = fminf(zb, B.Mu0 < 0.0f ? kInf : qu0);
+    exit = fminf(fminf(exit, B.Mu1 > 0.0f ? kInf : qu1), fminf(B.Mv0 < 0.0f ? kInf : qv0, B.Mv1 > 0.0f ? kInf : qv1));
+    near = fmaxf(__builtin_fmaf(enter, -kFrontMargin, enter) - B.pad, B.zlo);
+    exit = __builtin_fmaf(fabsf(exit), kFrontMargin, exit) + B.pad;
+    return near <= exit && near <= B.zhi;
+}
+
+// Whether the ellipsoid of a record can meet a ray of the bundle, and a lower bound of the depth of
+// any hit (with margin). Written so that NaN keeps the leaf.
+__device__ inline bool ellipsoid_meets(const Bundle &B, float Q, const float4 r0, const float4 r1, const float4 r2,
+                                       const float4 r3, float &near)
+{
+    const float a[3][3] = {{r0.x, r0.y, r0.z}, {r0.w, r1.x, r1.y}, {r1.z, r1.w, r2.x}};
+    const float D[3] = {r2.y, r2.z, r2.w};
+    float Z[3], U[3], V[3], s[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        Z[k] = B.sg * pick(B.ax, a[k][0], a[k][1], a[k][2]);
+        U[k] = pick(B.ax, a[k][1], a[k][2], a[k][0]);
+        V[k] = pick(B.ax, a[k][2], a[k][0], a[k][1]);
+        s[k] = __builtin_amdgcn_rcpf(D[k]);
+    }
+    const float mz = B.sg * pick(B.ax, r3.x, r3.y, r3.z) - B.z0, mu = pick(B.ax, r3.y, r3.z, r3.x),
+                mv = pick(B.ax, r3.z, r3.x, r3.y);
+    // support of the ellipsoid along the plane normal X - m Z
+    auto support = [&](const float *X, float m) {
+        float e = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const float w = (X[k] - m * Z[k]) * s[k];
+            e = __builtin_fmaf(w, w, e);
+        }
+        return __builtin_amdgcn_sqrtf(Q * e) * 1.0001f + B.pad;
+    };
+    bool out = (mu - B.Au1 - mz * B.Mu1) > support(U, B.Mu1);
+    out = out || (B.Au0 + mz * B.Mu0 - mu) > support(U, B.Mu0);
+    out = out || (mv - B.Av1 - mz * B.Mv1) > support(V, B.Mv1);
+    out = out || (B.Av0 + mz * B.Mv0 - mv) > support(V, B.Mv0);
+    float ez = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) ez = __builtin_fmaf(Z[k] * s[k], Z[k] * s[k], ez);
+    ez = __builtin_amdgcn_sqrtf(Q * ez) * 1.0001f + B.pad;
+    out = out || mz + ez < B.zlo;
+    // the centre line against the ellipsoid grown by the tube's half widths at its far end: a hit at
+    // depth z lies within delta (whitened) of the line's point at z
+    const float cu = 0.5f * (B.Mu0 + B.Mu1), cv = 0.5f * (B.Mv0 + B.Mv1);
+    const float zf = fmaxf(mz + ez, 0.0f);
+    const float wu = 0.5f * ((B.Au1 - B.Au0) + zf * (B.Mu1 - B.Mu0)), wv = 0.5f * ((B.Av1 - B.Av0) + zf * (B.Mv1 - B.Mv0));
+    const float xz = -mz, xu = 0.5f * (B.Au0 + B.Au1) - mu, xv = 0.5f * (B.Av0 + B.Av1) - mv;
+    float y[3], e[3], g2 = 0.0f, gd = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        y[k] = Z[k] * xz + U[k] * xu + V[k] * xv;
+        e[k] = Z[k] + U[k] * cu + V[k] * cv;
+        const float p = D[k] * U[k] * wu, q = D[k] * V[k] * wv;
+        g2 += p * p + q * q;
+        gd += p * q;
+    }
+    const float u0 = D[1] * D[2] * (y[1] * e[2] - y[2] * e[1]), u1 = D[0] * D[2] * (y[2] * e[0] - y[0] * e[2]),
+                u2 = D[0] * D[1] * (y[0] * e[1] - y[1] * e[0]);
+    const float d0 = D[0] * e[0], d1 = D[1] * e[1], d2 = D[2] * e[2];
+    const float ia = __builtin_amdgcn_rcpf(d0 * d0 + d1 * d1 + d2 * d2);
+    const float b = D[0] * y[0] * d0 + D[1] * y[1] * d1 + D[2] * y[2] * d2;
+    const float hh = (u0 * u0 + u1 * u1 + u2 * u2) * ia;
+    const float rr = __builtin_amdgcn_sqrtf(Q) + __builtin_amdgcn_sqrtf(g2 + 2.0f * fabsf(gd));
+    const float disc = rr * rr * 1.001f - hh;
+    out = out || disc < 0.0f;
+    const float zc = -b * ia;
+    // rounding of t1 (and of zc): an error of |x| ulp in y moves it by D / |d'| of that
+    const float slack = 2e-7f * (fabsf(xz) + fabsf(xu) + fabsf(xv)) * fmaxf(fmaxf(D[0], D[1]), D[2]) *
+                            __builtin_amdgcn_sqrtf(ia) + kFrontMargin * fabsf(zc) + B.pad;
+    // A ray enters in front of its point nearest to the centre. With w the ray's (whitened) offset from
+    // the line at zc and w1 its change per depth, that point lies (<q, w1> + <w, d' + w1>) / |d' + w1|^2
+    // from zc, |q| <= rr, |w| <= delta, |w1| <= delta / zf; used where |w1| <= |d'| / 2
+    const float delta = rr - __builtin_amdgcn_sqrtf(Q), w1 = delta * __builtin_amdgcn_rcpf(zf);
+    const float behind = 4.0f * rr * w1 * ia + 2.0f * delta * __builtin_amdgcn_sqrtf(ia);
+    out = out || (w1 * w1 * ia <= 0.25f && zc + behind * 1.001f + slack < B.zfrom);
+    // fmaxf returns the other operand for a NaN
+    const float zn = fmaxf(mz - ez, zc - __builtin_amdgcn_sqrtf(disc * ia));
+    near = fmaxf(zn - slack, B.zfrom);
+    out = out || near > B.zhi;
+    return !out;
+}
+
+// min of two keys (never NaN) as the bare instruction
+__device__ inline double min_bare(double a, double b)
+{
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// Scenes of up to this many Gaussians are walked where a launch has packets enough to fill the chip: a frontier
+// has fixed costs (1000 Gaussians, 588x587: 100 us walked, 115 in windows; 3000: 248 and 232).
+constexpr int64_t kFrontFew = 2048;
+constexpr int kFrontDrain = 32;  // lanes with a final hit that make a drain step worth while
+constexpr int kFrontDefault = 24;
+
+// GENERAL: with work counters and the paper variant's second phase.
+template <int K, bool GENERAL>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_render_front(
+    const float4 *__restrict__ records, const float4 *__restrict__ nodes, const int32_t *__restrict__ gidx,
+    const int32_t *__restrict__ inv, const Ptrs ptr, const RenderParams P)
+{
+    __shared__ FrontLds F;
+    __shared__ LaneCold cold;
+    const int lane = threadIdx.x;
+    int64_t iter_pkt = 0;
+    const int xcd = xcd_id();
+    int qi = 0;
+    FwdCount cnt{};
+    for (;;) {
+        const int64_t pkt = next_packet(P, ptr.queue, lane, xcd, qi, iter_pkt);
+        if (pkt >= P.n_packets) break;
+        if (GENERAL) ++cnt.pkt;
+        LaneState S;
+        bool zc, lists;
+        {
+            const LaneRay LR = lane_ray(P, ptr, pkt, lane);
+            S.ray = LR.ray;
+            const bool wanted = LR.valid && P.n_gauss > 0 && LR.tmax > P.t_min;
+            lane_reset(S, cold, wanted, lane);
+            zc = ptr.set[LR.si].zero_colour != 0;
+            lists = P.lists && ptr.set[LR.si].list != nullptr;
+            // hits are taken with start < key < stop
+            F.start[lane] = __longlong_as_double(__double_as_longlong(bound_key(P.t_min)) - 1);
+            F.stop[lane] = bound_key(LR.tmax);
+            F.from[lane] = P.t_min;
+            S.last = F.start[lane];
+        }
+        ListCursor LC{0, -1, 0, 0, -1, true};
+        HitBuf<K> hb;
+        bool redo = false;
+        // groups of rays along one axis (most packets are one group)
+        uint64_t todo = wave_ballot(S.live);
+        while (todo && !redo) {
+            const int leader = __builtin_ctzll(todo);
+            auto of_leader = [&](float x) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), leader)); };
+            const float lx = of_leader(S.ray.dx), ly = of_leader(S.ray.dy), lz = of_leader(S.ray.dz);
+            Bundle B;
+            B.ax = fabsf(lx) >= fabsf(ly) && fabsf(lx) >= fabsf(lz) ? 0 : (fabsf(ly) >= fabsf(lz) ? 1 : 2);
+            B.sg = pick(B.ax, lx, ly, lz) >= 0.0f ? 1.0f : -1.0f;
+            // the lane's direction and origin along z: z(t) = ozr + t dz
+            auto dz_of = [&]() { return B.sg * pick(B.ax, S.ray.dx, S.ray.dy, S.ray.dz); };
+            auto ozr_of = [&]() { return B.sg * pick(B.ax, S.ray.ox, S.ray.oy, S.ray.oz) - B.z0; };
+            uint64_t grp;  // the group's rays
+            {
+                const float dz = dz_of();
+                const float du = pick(B.ax, S.ray.dy, S.ray.dz, S.ray.dx), dv = pick(B.ax, S.ray.dz, S.ray.dx, S.ray.dy);
+                grp = wave_ballot(fabsf(du) <= 2.0f * dz && fabsf(dv) <= 2.0f * dz) & todo & wave_ballot(S.live);
+                if (!grp) {  // a direction without a largest component (not a number)
+                    redo = true;
+                    break;
                 }
-                const uint64_t hmask = wave_ballot(h2 <= P.Q) & live_now;
-                if (!hmask) return;
-                const float t1 = ellipsoid_t1(hg, r2, h2, P.Q);
-                const double k = hit_key(t1, gid);
-                const uint64_t cmask = hmask & wave_ballot(t1 >= P.t_min) & wave_ballot(t1 < tmax) &
-                                       wave_ballot(k > last) & wave_ballot(k < hb.last());
-                const bool cand = __builtin_amdgcn_inverse_ballot_w64(cmask);
-                if (COUNT) c_lbuf += __popcll(cmask);
-                if (cmask) {
-                    // every lane runs the insertion network; lanes without a candidate insert
-                    // the empty key, which moves nothing
-                    hb.insert(cand ? k : kNoHit);
-                    if (hb.last() != kNoHit) t_hi_w = widen(fminf(tmax, hit_key_t(hb.last())), sl.pad);
-                }
-            };
-
-            if (BRUTE) {
-                for (int64_t j = 0; j < P.n_gauss; ++j) leaf(j);
-            } else {
-                // While-while traversal: descend internal nodes until a leaf is reached (or the
-                // stack runs dry), then test that leaf; the hit buffer changes only in the leaf step.
-                // The walk is specialised on the wave's direction octant.
-                RS_WALK_BVH()
+                const bool on = __builtin_amdgcn_inverse_ballot_w64(grp);
+                const float oz = B.sg * pick(B.ax, S.ray.ox, S.ray.oy, S.ray.oz);
+                B.z0 = wave_min(on ? oz : kInf);
+                B.pad = 2e-6f * wave_max(on ? fabsf(S.ray.ox) + fabsf(S.ray.oy) + fabsf(S.ray.oz) : 0.0f);
             }
-            if (overflow) {
-                if (lane == 0) atomicOr(ptr.status, kStatusStack);
-                live = false;
+            float held = 0.0f;  // Gaussians in the bundle, by volume
+            if (P.root >= 0) {
+                const float4 n0 = nodes[0], n1 = nodes[1], n2 = nodes[2];
+                const float lx = fminf(n0.x, n1.z), ly = fminf(n0.y, n1.w), lz = fminf(n0.z, n2.x);
+                const float hx = fmaxf(n0.w, n2.y), hy = fmaxf(n1.x, n2.z), hz = fmaxf(n1.y, n2.w);
+                const float za = (B.sg > 0.0f ? pick(B.ax, lx, ly, lz) : -pick(B.ax, hx, hy, hz)) - B.z0;
+                const float zb = (B.sg > 0.0f ? pick(B.ax, hx, hy, hz) : -pick(B.ax, lx, ly, lz)) - B.z0;
+                const float eu = pick(B.ax, hy - ly, hz - lz, hx - lx), ev = pick(B.ax, hz - lz, hx - lx, hy - ly);
+                const float dz = dz_of(), ozr = ozr_of(), idz = 1.0f / dz;
+                const bool on = __builtin_amdgcn_inverse_ballot_w64(grp);
+                const float reach = __builtin_fmaf(hit_key_t(F.stop[lane]), dz, ozr);
+                const float z1 = fminf(zb, wave_max(on ? reach : 0.0f)), z0 = fmaxf(za, 0.0f);
+                if (z1 > z0) {
+                    // the bundle's cross-section at both ends of the scene
+                    const float mu = pick(B.ax, S.ray.dy, S.ray.dz, S.ray.dx) * idz, mv = pick(B.ax, S.ray.dz, S.ray.dx, S.ray.dy) * idz;
+                    const float au = pick(B.ax, S.ray.oy, S.ray.oz, S.ray.ox) - ozr * mu, av = pick(B.ax, S.ray.oz, S.ray.ox, S.ray.oy) - ozr * mv;
+                    auto span = [&](float x) { return wave_max(on ? x : -kInf) - wave_min(on ? x : kInf); };
+                    const float wu = fmaxf(span(au + z0 * mu), span(au + z1 * mu)), wv = fmaxf(span(av + z0 * mv), span(av + z1 * mv));
+                    held = fminf(wu, eu) * fminf(wv, ev) * (z1 - z0) * float(P.n_gauss) / (eu * ev * (zb - za));
+                }
+            }
+            todo &= ~grp;
+            // rays that share little: most leaves of the bundle would be tested for nothing
+            if (held > kFrontHeld) {
+                redo = true;
                 break;
             }
-
-            // composite this round's hits front to back; alpha is recomputed from the record
-            // with the leaf test's own arithmetic. The buffer is consumed from its front.
-            const double round_last = hb.last();
-            bool more = true;
-            // the sorted position of the buffer's front key is looked up one step ahead, so its
-            // latency overlaps the previous step (an empty key reads position 0, unused)
-            int32_t js_next = inv[hb.front() != kNoHit ? hit_key_gid(hb.front()) : 0u];
-            for (int s = 0; s < hb.size; ++s) {
-                const double key_s = hb.front();
-                const int32_t js_s = js_next;
-                hb.pop_front();
-                js_next = inv[hb.front() != kNoHit ? hit_key_gid(hb.front()) : 0u];
-                const bool act = more && live && key_s != kNoHit;
-                const uint64_t act_mask = wave_ballot(act);
-                more = act_mask != 0;
-                if (!more) break;
-                if (COUNT) c_lcomp += __popcll(act_mask);
-                const uint32_t gid = hit_key_gid(key_s);
-                uint32_t entry = kListIdle;
-                if (paper && phase2) {
-                    if (act) {
-                        if (T2 < P.eps2 || A.n + extra >= P.max_hits) {
-                            live = false;  // the second phase ends before this hit
-                        } else {
-                            float4 r0, r1, r2, r3;
-                            float t1, h2;
-                            HitGeom hg;
-                            const float al = hit_alpha_at(js_s, ray, records, P.Q, r0, r1, r2, r3, t1, h2, hg);
-                            entry = gid | kListSecond;
-                            T2 *= 1.0f - al;
-                            ++extra;
-                            last = key_s;
-                        }
+            int rounds = 0;
+            // rounds, until the group's rays have stopped or run out of hits
+            for (uint64_t on_mask = grp & wave_ballot(S.live); on_mask && !redo; on_mask = grp & wave_ballot(S.live)) {
+                if (GENERAL) ++cnt.round;
+                hb.clear();
+                double cap = F.stop[lane];
+                F.start[lane] = S.last;
+                rejoin();
+                float Tv = S.A.T, tv = 0.0f;  // T behind every hit buffered so far, and the farthest one's depth
+                const uint64_t began = on_mask;
+                int nA = 0, nN = 0, nP = 0, nR = 0, n_on;
+                {
+                    const bool on = __builtin_amdgcn_inverse_ballot_w64(on_mask);
+                    const float dz = dz_of(), ozr = ozr_of();
+                    const float tl = F.from[lane];
+                    const float zl = wave_min(on ? __builtin_fmaf(tl, dz, ozr) : kInf);
+                    B.zfrom = fmaxf(zl - kFrontMargin * fabsf(zl) - B.pad, 0.0f);
+                    B.zlo = fmaxf(zl - kFrontBack * fabsf(zl) - B.pad, 0.0f);
+                    const float zh = wave_max(on ? __builtin_fmaf(hit_key_t(cap), dz, ozr) : -kInf);
+                    B.zhi = zh + kFrontMargin * fabsf(zh) + B.pad;
+                    bundle_bounds(B, S.ray, on, ozr, dz);
+                    n_on = __popcll(on_mask);
+                }
+                float S0 = 0.0f, S1 = kInf, dS = kInf;  // the window [S0, S1)
+                __syncthreads();
+                if (P.root >= 0) {
+                    const float4 n0 = nodes[0], n1 = nodes[1], n2 = nodes[2];
+                    const float lx = fminf(n0.x, n1.z), ly = fminf(n0.y, n1.w), lz = fminf(n0.z, n2.x);
+                    const float hx = fmaxf(n0.w, n2.y), hy = fmaxf(n1.x, n2.z), hz = fmaxf(n1.y, n2.w);
+                    float near;
+                    if (!box_meets(B, lx, ly, lz, hx, hy, hz, near)) near = kInf;
+                    near = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(near)));
+                    const float zf = (B.sg > 0.0f ? pick(B.ax, hx, hy, hz) : -pick(B.ax, lx, ly, lz)) - B.z0;
+                    // the first window: the share of the root's depth range that may hold a window's leaves
+                    // (boxes overlap a bundle that their centres are far from: some tens per Gaussian held)
+                    if (near < kInf) {
+                        F.ar[0] = P.root;
+                        nA = 1;
+                        S0 = near;
+                        dS = fmaxf((zf - near) * fminf(fmaxf(kFrontFirst / fmaxf(held, 1e-3f), 1.0f / 64.0f), 0.125f),
+                                   1e-5f * fabsf(zf) + 1e-20f);
+                        S1 = S0 + dS;
                     }
                 } else {
-                    HitData H;
-                    composite_hit(act, gid, js_s, ray, records, ptr.rgb, zc, P, A, H);
-                    if (act) {
-                        entry = gid;
-                        last = key_s;
-                        if (A.T < kMinNormal && H.Tk >= kMinNormal) {
-                            Tz = H.Tk;
-                            z = A.n - 1;
+                    F.raw[0] = ~P.root;
+                    nR = 1;
+                }
+                __syncthreads();
+
+                // every window tests leaves or moves on; the bound on their number is a backstop
+                int windows = 0;
+                for (bool more = true; more;) {
+                    if (++windows > kFrontWindows) {
+                        redo = true;
+                        break;
+                    }
+                    // ---- expand the window's nodes, and test the leaves found against the bundle
+                    bool forced = false;  // the leaf pool ran full first
+                    while (nA > 0 || nR > 0) {
+                        if (nR >= kWave || nA == 0) {
+                            if (nP > kFrontLeaves - kWave) {
+                                forced = true;
+                                break;
+                            }
+                            const int m = nR < kWave ? nR : kWave;
+                            const int32_t js = F.raw[nR - m + (lane < m ? lane : 0)];
+                            nR -= m;
+                            const float4 r0 = records[4 * int64_t(js)], r1 = records[4 * int64_t(js) + 1],
+                                         r2 = records[4 * int64_t(js) + 2], r3 = records[4 * int64_t(js) + 3];
+                            float near;
+                            const uint64_t km = wave_ballot(ellipsoid_meets(B, P.Q, r0, r1, r2, r3, near) && lane < m);
+                            if (__builtin_amdgcn_inverse_ballot_w64(km)) {
+                                const int at = nP + int(lanes_below(km));
+                                F.pz[at] = near;
+                                F.pr[at] = js;
+                            }
+                            nP += __popcll(km);
+                            __syncthreads();
+                            continue;
+                        }
+                        if (nA >= kFrontActive) {
+                            redo = true;
+                            break;
+                        }
+                        // children: at most 2 m more leaves and nodes
+                        int m = nA < kWave ? nA : kWave;
+                        const int room_r = (kFrontRaw - nR) / 2, room_a = (kFrontActive - nA + 1) / 2;
+                        m = m < room_r ? m : room_r;
+                        m = m < room_a ? m : room_a;
+                        const bool mine = lane < m;
+                        const int32_t node = F.ar[nA - m + (mine ? lane : 0)];
+                        nA -= m;
+                        const float4 *nd = nodes + 4 * int64_t(node);
+                        const float4 n0 = nd[0], n1 = nd[1], n2 = nd[2];
+                        const int2 lr = *reinterpret_cast<const int2 *>(nd + 3);
+                        float ln, rn;
+                        const uint64_t hl = wave_ballot(box_meets(B, n0.x, n0.y, n0.z, n0.w, n1.x, n1.y, ln) && mine);
+                        const uint64_t hr = wave_ballot(box_meets(B, n1.z, n1.w, n2.x, n2.y, n2.z, n2.w, rn) && mine);
+                        if (GENERAL) {
+                            cnt.node += m;
+                            cnt.lchild += __popcll(hl) + __popcll(hr);
+                        }
+                        const bool full = nN > kFrontNodes - 2 * kWave;  // no room beyond the window: expand at once
+                        __syncthreads();
+#pragma unroll
+                        for (int c = 0; c < 2; ++c) {
+                            const uint64_t h = c ? hr : hl;
+                            const int32_t ref = c ? lr.y : lr.x;
+                            const float near = c ? rn : ln;
+                            const uint64_t leafs = wave_ballot(ref < 0), now = full ? ~0ull : wave_ballot(near < S1);
+                            const uint64_t mr = h & leafs, ma = h & ~leafs & now, mn = h & ~leafs & ~now;
+                            if (__builtin_amdgcn_inverse_ballot_w64(mr)) F.raw[nR + int(lanes_below(mr))] = ~ref;
+                            if (__builtin_amdgcn_inverse_ballot_w64(ma)) F.ar[nA + int(lanes_below(ma))] = ref;
+                            if (__builtin_amdgcn_inverse_ballot_w64(mn)) {
+                                const int at = nN + int(lanes_below(mn));
+                                F.nz[at] = near;
+                                F.nr[at] = ref;
+                            }
+                            rejoin();
+                            nR += __popcll(mr);
+                            nA += __popcll(ma);
+                            nN += __popcll(mn);
+                        }
+                        __syncthreads();
+                    }
+                    if (redo) break;
+
+                    // ---- the window's leaves in depth order: a counting sort over 64 depth bins
+                    F.hist[lane] = 0u;
+                    __syncthreads();
+                    float take = S1;
+                    if (forced) {
+                        // the pool is full while nodes of the window are left: bins over all it holds
+                        float far = S0;
+                        for (int b = 0; b < nP; b += kWave)
+                            if (b + lane < nP) far = fmaxf(far, F.pz[b + lane]);
+                        take = wave_max(far) * 1.0001f + 1e-20f;
+                        dS *= 0.25f;
+                    }
+                    const float wbin = take < kInf ? (take - S0) * (1.0f / 64.0f) : 0.0f;
+                    const float inv_w = wbin > 0.0f ? 1.0f / wbin : 0.0f;
+                    auto bin_of = [&](float z) { return int(fminf(fmaxf((z - S0) * inv_w, 0.0f), 63.0f)); };
+                    for (int b = 0; b < nP; b += kWave) {
+                        const int i = b + lane;
+                        if (i < nP && F.pz[i] < take) atomicAdd(&F.hist[bin_of(F.pz[i])], 1u);
+                        rejoin();
+                    }
+                    __syncthreads();
+                    const int in_bin = int(F.hist[lane]);
+                    int cum = in_bin;
+#pragma unroll
+                    for (int d = 1; d < kWave; d <<= 1) {
+                        const int x = __shfl_up(cum, d);
+                        if (lane >= d) cum += x;
+                    }
+                    // whole bins, as many as fit; where the first one with leaves is too many by itself, some
+                    // of it (without progress in depth)
+                    const uint64_t fit = wave_ballot(cum <= kFrontSorted), none = wave_ballot(cum == 0);
+                    const bool partial = fit != ~0ull && (fit & ~none) == 0;
+                    const int nbins = __popcll(partial ? none : fit) + (partial ? 1 : 0);
+                    // a full pool keeps its nearest leaves alone, and this round ends in front of the others;
+                    // where even those are too many, some of them are tested now
+                    const float zcut = S0 + float(nbins) * wbin;
+                    const bool cut = forced && !partial && zcut > B.zfrom * (1.0f + 4.0f * kFrontMargin) + 4.0f * B.pad;
+                    const int total = __builtin_amdgcn_readlane(cum, nbins - 1);
+                    const int nS = cut ? 0 : (total < kFrontSorted ? total : kFrontSorted);
+                    F.hist[lane] = uint32_t(cum - in_bin);
+                    __syncthreads();
+                    int kept = 0;
+                    float zleft = kInf;  // nearest leaf or node left for later
+                    for (int b = 0; b < nP; b += kWave) {
+                        const int i = b + lane;
+                        const bool in = i < nP;
+                        const float z = in ? F.pz[i] : kInf;
+                        const int32_t js = in ? F.pr[i] : 0;
+                        const int bin = bin_of(z);
+                        bool sel = z < take && bin < nbins;
+                        if (cut) {
+                            sel = !sel;  // what does not stay
+                        } else if (sel) {
+                            const int at = int(atomicAdd(&F.hist[bin], 1u));
+                            if (at < kFrontSorted) {
+                                F.sz[at] = forced ? S0 : S0 + float(bin) * wbin;
+                                F.sr[at] = js;
+                            } else {
+                                sel = false;
+                            }
+                        }
+                        const uint64_t km = wave_ballot(in && !sel);
+                        __syncthreads();
+                        if (in && !sel) {
+                            const int at = kept + int(lanes_below(km));
+                            F.pz[at] = z;
+                            F.pr[at] = js;
+                            zleft = fminf(zleft, z);
+                        }
+                        kept += __popcll(km);
+                        __syncthreads();
+                    }
+                    nP = kept;
+                    if (cut) {
+                        const double c = bound_key(fmaxf((zcut - ozr_of()) * (1.0f / dz_of()), 0.0f));
+                        cap = c < cap ? c : cap;
+                        B.zhi = fminf(B.zhi, zcut + kFrontMargin * zcut + B.pad);
+                    }
+                    // everything in front of `done` has been found
+                    float done = forced || partial ? S0 : (nbins == kWave ? S1 : S0 + float(nbins) * wbin);
+                    for (int b = 0; b < nN; b += kWave)
+                        if (b + lane < nN) zleft = fminf(zleft, F.nz[b + lane]);
+                    const float zmin = wave_min(zleft);
+                    if (!forced) {
+                        if (zmin > B.zhi) done = kInf;  // nothing is left, or nothing in reach
+                        more = done < kInf;
+                    }
+
+                    // ---- test the leaves ray by ray, two at a time (their fetches and arithmetic overlap);
+                    // behind the last ones, consume what the window settled
+                    int32_t srv = 0, szv = 0;
+                    int32_t reach = __float_as_int(B.zhi);  // depths are >= 0, so their bits order like integers
+                    for (int i = 0;; i += 2) {
+                        const bool end = i >= nS;
+                        double ka = kNoHit, kb = kNoHit;
+                        uint64_t ma = 0, mb = 0;
+                        float oma = 1.0f, omb = 1.0f, ta = 0.0f, tb = 0.0f;
+                        int32_t front = __float_as_int(done);
+                        if (!end) {
+                            const int ia = i & (kWave - 1);
+                            if (ia == 0) {
+                                const int at = i + lane < nS ? i + lane : nS - 1;
+                                srv = F.sr[at];
+                                szv = __float_as_int(F.sz[at]);
+                            }
+                            front = __builtin_amdgcn_readlane(szv, ia);
+                            if (front > reach) continue;
+                            const int64_t ja = __builtin_amdgcn_readlane(srv, ia), jb = __builtin_amdgcn_readlane(srv, ia + 1);
+                            const float4 a0 = records[4 * ja], a1 = records[4 * ja + 1], a2 = records[4 * ja + 2],
+                                         a3 = records[4 * ja + 3];
+                            const float4 b0 = records[4 * jb], b1 = records[4 * jb + 1], b2 = records[4 * jb + 2],
+                                         b3 = records[4 * jb + 3];
+                            const uint32_t ga = uint32_t(gidx[ja]), gb = uint32_t(gidx[jb]);
+                            HitGeom ha, hb2;
+                            const float h2a = ellipsoid_h2(S.ray, a0, a1, a2, a3, ha);
+                            const float h2b = ellipsoid_h2(S.ray, b0, b1, b2, b3, hb2);
+                            asm volatile("" ::"s"(ga), "s"(gb));  // the index loads are issued with the records'
+                            if (GENERAL) {
+                                cnt.leaf += i + 1 < nS ? 2 : 1;
+                                cnt.lleaf += __popcll(on_mask) * (i + 1 < nS ? 2 : 1);
+                            }
+                            ma = wave_ballot(h2a <= P.Q) & on_mask;
+                            mb = wave_ballot(h2b <= P.Q) & (i + 1 < nS ? on_mask : 0ull);
+                            if ((ma | mb) == 0) continue;
+                            ta = ellipsoid_t1(ha, a2, h2a, P.Q);
+                            tb = ellipsoid_t1(hb2, b2, h2b, P.Q);
+                            ka = hit_key(ta, ga);
+                            kb = hit_key(tb, gb);
+                            oma = 1.0f - a3.w * __expf(-0.5f * h2a);
+                            omb = 1.0f - b3.w * __expf(-0.5f * h2b);
+                            ma &= wave_ballot(ka < cap);
+                            mb &= wave_ballot(kb < cap);
+                            const uint64_t la = ma & ~wave_ballot(ka > S.last), lb = mb & ~wave_ballot(kb > S.last);
+                            if (la | lb) {
+                                // consumed in an earlier round (or in front of t_min), or found too late
+                                if ((la & wave_ballot(ka > F.start[lane])) | (lb & wave_ballot(kb > F.start[lane]))) {
+                                    redo = true;
+                                    break;
+                                }
+                                ma &= ~la;
+                                mb &= ~lb;
+                            }
+                            if ((ma | mb) == 0) continue;
+                        }
+                        if (end || ((ma | mb) & wave_ballot(hb.key[K - 2] != kNoHit))) {
+                            // Consume the hits in front of `front` (their order is final): behind the last window
+                            // all of them, else while many lanes have one or a lane with one has a full buffer
+                            const int least = end ? (more ? 65 : 1) : kFrontDrain;
+                            const float tf = (__int_as_float(front) - ozr_of()) * (1.0f / dz_of());
+                            double key = hb.front();
+                            int32_t js = inv[key != kNoHit ? hit_key_gid(key) : 0u];
+                            for (;;) {
+                                const uint64_t am = grp & wave_ballot(S.live) & wave_ballot(key != kNoHit) &
+                                                    wave_ballot(hit_key_t(key) < tf) & wave_ballot(key < cap);
+                                if (am == 0) break;
+                                if (__popcll(am) < least && (am & wave_ballot(hb.key[K - 2] != kNoHit)) == 0) break;
+                                if (GENERAL) cnt.lcomp += __popcll(am);
+                                const bool act = __builtin_amdgcn_inverse_ballot_w64(am);
+                                const double key_s = key;
+                                const int32_t js_s = js;
+                                if (act) hb.pop_front();
+                                rejoin();
+                                key = hb.front();
+                                js = inv[key != kNoHit ? hit_key_gid(key) : 0u];
+                                consume<GENERAL>(act, key_s, js_s, S, cold, records, ptr, P, zc, lists, LC, lane);
+                            }
+                            on_mask = grp & wave_ballot(S.live);
+                            if (end || !on_mask) break;
+                            ma &= on_mask;
+                            mb &= on_mask;
+                            if ((ma & ~wave_ballot(ka > S.last)) | (mb & ~wave_ballot(kb > S.last))) {
+                                redo = true;
+                                break;
+                            }
+                        }
+                        if (GENERAL) cnt.lbuf += __popcll(ma) + __popcll(mb);
+                        const bool ca = __builtin_amdgcn_inverse_ballot_w64(ma), cb = __builtin_amdgcn_inverse_ballot_w64(mb);
+                        if (ma) cap = min_bare(cap, hb.insert_out(ca ? ka : kNoHit));
+                        if (mb) cap = min_bare(cap, hb.insert_out(cb ? kb : kNoHit));
+                        // once the hits found so far bring T below eps1 whatever their order, none behind the
+                        // farthest of them is wanted
+                        Tv *= (ca ? oma : 1.0f) * (cb ? omb : 1.0f);
+                        tv = fmaxf(tv, fmaxf(ca ? ta : 0.0f, cb ? tb : 0.0f));
+                        const bool closed = Tv < 0.99f * P.eps1;
+                        if ((ma | mb) & wave_ballot(closed) && !(GENERAL && P.paper)) {
+                            const double far = __longlong_as_double(__double_as_longlong(bound_key(tv)) + (1ll << 32));
+                            cap = closed ? min_bare(cap, far) : cap;
+                            const float zr = wave_max(__builtin_amdgcn_inverse_ballot_w64(on_mask)
+                                                          ? __builtin_fmaf(hit_key_t(cap), dz_of(), ozr_of())
+                                                          : -kInf);
+                            reach = __float_as_int(zr + kFrontMargin * fabsf(zr) + B.pad);
                         }
                     }
-                    const bool stopped = act && stop_after(A, P);
-                    if (stopped) {
-                        if (paper && A.T < P.eps1)
-                            phase2 = true;  // stays live for the second phase
-                        else
-                            live = false;
-                    }
-                }
-                if (lists) list_append(ptr.pool, LC, entry, lane, stored, paper, ptr.status);
-            }
-            // a lane whose buffer did not fill has consumed all its hits
-            if (live && round_last == kNoHit) live = false;
-        }
+                    if (redo || !on_mask) break;
+                    if (forced || !more) continue;
 
-        if (lists) {
-            list_close(ptr.pool, LC, lane);
-            if (COUNT) {
-                c_rows += uint64_t(LC.rows);
-                c_slots += uint64_t(LC.slots);
+                    // ---- the next window starts at the nearest thing left
+                    {
+                        const bool on = __builtin_amdgcn_inverse_ballot_w64(on_mask);
+                        const float dz = dz_of(), ozr = ozr_of();
+                        const float zh = wave_max(on ? __builtin_fmaf(hit_key_t(cap), dz, ozr) : -kInf);
+                        B.zhi = zh + kFrontMargin * fabsf(zh) + B.pad;
+                        if (2 * __popcll(on_mask) <= n_on) {  // half of the rays have stopped: a tighter bundle
+                            bundle_bounds(B, S.ray, on, ozr, dz);
+                            n_on = __popcll(on_mask);
+                        }
+                    }
+                    if (nS < 64) dS *= 2.0f;
+                    if (nS > 144) dS *= 0.5f;
+                    S0 = fmaxf(done, zmin);
+                    S1 = S0 + fmaxf(dS, 1e-5f * S0 + 1e-20f);
+                    int keep_n = 0;
+                    for (int b = 0; b < nN; b += kWave) {
+                        const int i = b + lane;
+                        const bool in = i < nN;
+                        const float z = in ? F.nz[i] : kInf;
+                        const int32_t ref = in ? F.nr[i] : 0;
+                        const uint64_t ma = wave_ballot(z < S1), mk = wave_ballot(in) & ~ma;
+                        __syncthreads();
+                        if (__builtin_amdgcn_inverse_ballot_w64(ma)) F.ar[nA + int(lanes_below(ma))] = ref;
+                        if (__builtin_amdgcn_inverse_ballot_w64(mk)) {
+                            const int at = keep_n + int(lanes_below(mk));
+                            F.nz[at] = z;
+                            F.nr[at] = ref;
+                        }
+                        nA += __popcll(ma);
+                        keep_n += __popcll(mk);
+                        __syncthreads();
+                    }
+                    nN = keep_n;
+                }
+                if (redo) break;
+                // a lane that lost nothing has consumed all its hits, every other live one those in front of
+                // its cap
+                if (__builtin_amdgcn_inverse_ballot_w64(on_mask) && !(cap < F.stop[lane])) S.live = false;
+                rejoin();
+                const uint64_t left = grp & wave_ballot(S.live);
+                const float from = hit_key_t(cap);
+                const uint64_t ahead = wave_ballot(S.last > F.start[lane]) | wave_ballot(from > F.from[lane]);
+                redo = left != 0 && (((left & ahead) == 0 && left == began) || ++rounds > kFrontRounds);
+                if (__builtin_amdgcn_inverse_ballot_w64(grp)) F.from[lane] = fmaxf(F.from[lane], from);
+                rejoin();
             }
         }
-        if (valid) {
-            const float orr = __builtin_fmaf(A.T, bgr, A.Cr), og = __builtin_fmaf(A.T, bgg, A.Cg),
-                        ob = __builtin_fmaf(A.T, bgb, A.Cb);
-            S.out_rgb[3 * ray_id] = orr;
-            S.out_rgb[3 * ray_id + 1] = og;
-            S.out_rgb[3 * ray_id + 2] = ob;
-            if (S.fin) {
-                S.fin[ray_id] = make_float4(orr, og, ob, A.T);
-                const uint64_t kb = A.n > 0 ? uint64_t(__double_as_longlong(last)) : 0ull;
-                S.last[ray_id] = make_uint4(uint32_t(kb), uint32_t(kb >> 32), __float_as_uint(Tz),
-                                            z >= 0 ? uint32_t(A.n - 1 - z) : 0xffffffffu);
-            }
-            if (lists) S.list[ray_id] = make_int4(A.n, stored, LC.chunk, LC.rows);
+        const LaneRay LR = lane_ray(P, ptr, pkt, lane);
+        if (redo) {
+            // start over with the walk; the packet's first list chunk is used again
+            lane_reset(S, cold, LR.valid && P.n_gauss > 0 && LR.tmax > P.t_min, lane);
+            LC = ListCursor{0, LC.first, 0, 0, LC.first, true};
+            if (!walk_rounds<HitBuf<K>, false, false, GENERAL, GENERAL>(S, cold, LR, zc, lists, LC, records, nodes, gidx, inv,
+                                                                         ptr, P, hb, lane, cnt))
+                if (lane == 0) atomicOr(ptr.status, kStatusStack);
+        }
+        write_rays(S, cold, LR, ptr.set[LR.si], ptr, LC, lists, lane);
+        if (GENERAL) {
+            cnt.rows += uint64_t(LC.rows);
+            cnt.slots += uint64_t(LC.slots);
         }
     }
-    if (COUNT && lane == 0 && c_pkt > 0) {
-        atomicAdd(ptr.counters + 0, (unsigned long long)c_pkt);
-        atomicAdd(ptr.counters + 1, (unsigned long long)c_node);
-        atomicAdd(ptr.counters + 2, (unsigned long long)c_leaf);
-        atomicAdd(ptr.counters + 3, (unsigned long long)c_round);
-        atomicAdd(ptr.counters + 4, (unsigned long long)c_lleaf);
-        atomicAdd(ptr.counters + 5, (unsigned long long)c_lbuf);
-        atomicAdd(ptr.counters + 6, (unsigned long long)c_lcomp);
-        atomicAdd(ptr.counters + 7, (unsigned long long)c_lchild);
-        atomicAdd(ptr.counters + 12, (unsigned long long)c_rows);
-        atomicAdd(ptr.counters + 14, (unsigned long long)c_slots);
-    }
+    if (GENERAL) add_counts(cnt, ptr, lane);
 }
 
 // ------------------------------------------------- adjoint by re-traversal
@@ -1225,7 +2018,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(waves_for(K,
     const int32_t *__restrict__ inv, const Ptrs ptr, const RenderParams P)
 {
     constexpr bool kRev = true;
-    if (P.overflow_only && ptr.pool.hdr[1] == 0ull) return;  // every list is complete
+    if (P.overflow_only && uint32_t(ptr.pool.hdr[1]) == 0u) return;  // every list is complete
     const int lane = threadIdx.x;
     int64_t iter_pkt = 0;
     const int xcd = xcd_id();
@@ -1386,10 +2179,10 @@ __device__ inline void row_seek(const int32_t *__restrict__ prev, const int32_t 
 
 // Reads the row ending at `start` of `chunk` (its lane mask), moves `start` to the row's first
 // slot, and returns this lane's entry (kListIdle for a lane without one, or not live).
-__device__ inline uint32_t row_entry(const uint32_t *__restrict__ slots, int32_t chunk, int32_t &start, bool live,
-                                     int lane)
+__device__ inline uint32_t row_entry(const uint32_t *__restrict__ slots, int32_t chunk_slots, int32_t chunk,
+                                     int32_t &start, bool live, int lane)
 {
-    const uint32_t *row_end = slots + int64_t(chunk) * kChunkSlots + start;
+    const uint32_t *row_end = slots + int64_t(chunk) * chunk_slots + start;
     // the mask's address is wave-uniform: read it through the constant address space, so it is
     // a scalar load (the pool is only read by this kernel)
     typedef const __attribute__((address_space(4))) uint32_t *const_u32;
@@ -1444,12 +2237,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RS_LIST_WAVE
         int32_t start = fill[chunk];
         row_seek(prev, fill, chunk, start);
         uint32_t e = kListIdle;
-        if (chunk >= 0) e = row_entry(slots, chunk, start, live, lane);
+        if (chunk >= 0) e = row_entry(slots, ptr.pool.chunk_slots, chunk, start, live, lane);
         while (chunk >= 0) {
             int32_t nchunk = chunk, nstart = start;
             row_seek(prev, fill, nchunk, nstart);
             uint32_t ne = kListIdle;
-            if (nchunk >= 0) ne = row_entry(slots, nchunk, nstart, live, lane);
+            if (nchunk >= 0) ne = row_entry(slots, ptr.pool.chunk_slots, nchunk, nstart, live, lane);
             chunk = nchunk;
             start = nstart;
             const uint32_t cur = e;
@@ -1538,14 +2331,14 @@ __global__ void k_zero_queue(uint32_t *q)
     if (threadIdx.x < kXcdQueues) q[threadIdx.x] = 0u;
 }
 
-__global__ void k_zero_pool_header(unsigned long long *h)
+__global__ void k_zero_pool_header(unsigned long long *h, unsigned long long second)
 {
-    if (threadIdx.x < 2) h[threadIdx.x] = 0ull;
+    if (threadIdx.x < 2) h[threadIdx.x] = threadIdx.x ? second : 0ull;
 }
 
-void reset_pool(const ListPool &pool, hipStream_t st)
+void reset_pool(const ListPool &pool, int pkt_shift, hipStream_t st)
 {
-    if (pool.hdr) k_zero_pool_header<<<1, 64, 0, st>>>(pool.hdr);
+    if (pool.hdr) k_zero_pool_header<<<1, 64, 0, st>>>(pool.hdr, (unsigned long long)pkt_shift << 32);
 }
 
 static void zero(float *p, int64_t n, hipStream_t st)
@@ -1561,6 +2354,22 @@ struct KernArgs {
     const float4 *records, *nodes;
     const int32_t *gidx, *inv;
 };
+
+// workgroups of a plain grid: one per packet, in whole deals (see next_packet)
+static int plain_grid(int64_t n_packets)
+{
+    const int64_t deal = int64_t(kXcdQueues) * kXcdRun;
+    return int((n_packets + deal - 1) / deal * deal);
+}
+
+template <int K>
+static void launch_front(const KernArgs &a, const Ptrs &ptr, const RenderParams &P, hipStream_t st)
+{
+    if (P.count || P.paper)
+        k_render_front<K, true><<<a.grid, kWave, 0, st>>>(a.records, a.nodes, a.gidx, a.inv, ptr, P);
+    else
+        k_render_front<K, false><<<a.grid, kWave, 0, st>>>(a.records, a.nodes, a.gidx, a.inv, ptr, P);
+}
 
 template <int K>
 static void launch_k(Pass pass, const KernArgs &a, const Ptrs &ptr, const RenderParams &P, hipStream_t st)
@@ -1600,7 +2409,7 @@ void scatter_gacc(const BvhDesc &D, const float *quat, const rs_grads *grads, hi
 
 // One launch over up to kMaxSets ray sets sharing a layout (same count, same views).
 int launch_sets(const BvhDesc &D, const rs_gaussians *g, const rs_params *p, int nsets, const SetDesc *sets,
-                const ListPool &pool, Pass pass, hipStream_t st)
+                const ListRoom &room, Pass pass, hipStream_t st)
 {
     Layout L = make_layout(D.n);
     char *ws = D.ws;
@@ -1620,7 +2429,15 @@ int launch_sets(const BvhDesc &D, const rs_gaussians *g, const rs_params *p, int
     P.persistent = (p->flags & RS_PERSISTENT) ? 1 : 0;
     P.brute = (p->flags & RS_BRUTE_FORCE) ? 1 : 0;
     P.count = (p->flags & RS_COUNTERS) ? 1 : 0;
-    const int64_t packets = plan_packets(P, rays, tile_shift_of(p));
+    // the frontier kernel keeps no stack: a call that bounds the stack takes the walk. So do the sets of paths
+    // of several bounces: refracted rays of a packet go all ways (150k Gaussians, 640x361, three bounces: 7.7 ms
+    // walked, 9.2 to 22 otherwise).
+    P.front = pass == Pass::Forward && !P.brute && p->stack_depth == 0 && nsets <= 3 &&
+              (D.n > kFrontFew || packet_shift(rays, nsets, p, D.n) < 6);
+    const int pkt_shift = P.front && room.units == 0 ? packet_shift_no_lists(rays, nsets, p, D.n)
+                                                     : packet_shift(rays, nsets, p, D.n);
+    const ListPool pool = list_pool_at(room, chunk_slots_of(pkt_shift));
+    const int64_t packets = plan_packets(P, rays, pkt_shift == 6 ? tile_shift_of(p) : pkt_shift / 2, pkt_shift);
     P.packets_per_set = packets;
     P.n_packets = packets * nsets;
     P.strip_tiles = kStripTiles;
@@ -1653,7 +2470,7 @@ int launch_sets(const BvhDesc &D, const rs_gaussians *g, const rs_params *p, int
     ptr.gacc = reinterpret_cast<float *>(ws + L.gacc);
     ptr.pool = pool;
 
-    if (pass == Pass::Forward && P.lists) reset_pool(pool, st);
+    if (pass == Pass::Forward && P.lists) reset_pool(pool, pkt_shift, st);
     if (P.n_packets > 0) {
         KernArgs a;
         if (P.persistent) {
@@ -1664,8 +2481,7 @@ int launch_sets(const BvhDesc &D, const rs_gaussians *g, const rs_params *p, int
             const int64_t waves = int64_t(cus) * 24;  // up to 6 waves per SIMD (the most any variant fits)
             a.grid = int(waves < P.n_packets ? waves : P.n_packets);
         } else {
-            const int64_t deal = int64_t(kXcdQueues) * kXcdRun;
-            a.grid = int((P.n_packets + deal - 1) / deal * deal);
+            a.grid = plain_grid(P.n_packets);
         }
         a.records = reinterpret_cast<const float4 *>(ws + L.records);
         a.nodes = reinterpret_cast<const float4 *>(ws + L.nodes);
@@ -1678,6 +2494,15 @@ int launch_sets(const BvhDesc &D, const rs_gaussians *g, const rs_params *p, int
                 k_adjoint_list<true><<<a.grid, kWave, 0, st>>>(a.records, a.inv, ptr, P);
             else
                 k_adjoint_list<false><<<a.grid, kWave, 0, st>>>(a.records, a.inv, ptr, P);
+        } else if (P.front) {
+            // three buffer sizes: kbuf names the nearest
+            const int K = p->kbuf > 0 ? p->kbuf : kFrontDefault;
+            if (K <= 16)
+                launch_front<16>(a, ptr, P, st);
+            else if (K <= 24)
+                launch_front<24>(a, ptr, P, st);
+            else
+                launch_front<32>(a, ptr, P, st);
         } else {
             const int K = p->kbuf > 0 ? p->kbuf : 48;
             switch (K) {
@@ -1705,15 +2530,15 @@ int launch_render(const BvhDesc &D, const rs_gaussians *g, const rs_rays *rays, 
     S.zero_colour = (p->flags & RS_ZERO_COLOUR) ? 1 : 0;
     const int32_t cap = p->hit_list;
     S.state = state_at(state, rays->n, cap);
-    ListPool pool{nullptr, nullptr, nullptr, 0};
+    ListRoom pool{};
     if (state && cap > 0 && rays->n > 0) {
         const StateLayout sl = state_layout(rays->n, cap);
-        pool = list_pool_at(static_cast<char *>(state) + sl.pool, sl.chunks);
+        pool = ListRoom{static_cast<char *>(state) + sl.pool, sl.chunks};
     }
     if (!bwd) return launch_sets(D, g, p, 1, &S, pool, Pass::Forward, st);
     int e;
     zero_gacc(D, st);
-    if (pool.chunks > 0) {
+    if (pool.units > 0) {
         // stored lists first; the traversal adjoint then takes the rays whose list is
         // incomplete (it exits at once when the forward found the pool large enough).
         // The paper variant has no traversal form: its pool running out is an error.
