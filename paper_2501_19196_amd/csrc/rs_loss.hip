@@ -5,9 +5,9 @@
 // Gaussian window (zero outside the image); the gradient of mean SSIM is
 // App. A.7's (1/hw) ((E * w) + I^ (F * w) - I (G * w)).
 //
-// Three launches: k_ssim_maps (moments by separable LDS-tiled window sums,
-// the SSIM map reduced per tile, the E, F, G maps written), k_ssim_grad
-// (window sums of E, F, G, then the per-pixel gradient) and k_loss_total.
+// Three launches: k_ssim_maps (window moments, the SSIM map and the squared error summed per workgroup,
+// the E, F, G maps written), k_ssim_grad (window sums of E, F, G, then the per-pixel gradient) and
+// k_loss_total.
 #include <math.h>
 
 #include <mutex>
@@ -16,168 +16,223 @@
 
 namespace rs {
 
-constexpr int kLossTw = 32, kLossTh = 8;  // output tile (256 threads)
+// The window sums run down the image: a wave owns 64 columns of an image row taken as 3 w floats (pixel
+// and channel alike: a tap is 3 floats apart) and a band of rows. For each input row it puts the row's
+// values in LDS, a lane sums them across, and adds the sums to the output rows that they belong to, whose
+// partial sums stay in registers (a ring of 2 R + 1, in code unrolled over its phases). So a row is read
+// once per band, no barrier is needed, and each sum is taken in the order of the taps. Bound by vector
+// arithmetic: about 180 operations per channel of a pixel in k_ssim_maps and 90 in k_ssim_grad.
+// 1920x1080, loss and gradient: 98 us; 228 us with LDS tiles of 32x8 and vertical sums taken tap by tap from LDS.
+constexpr int kLossWaves = 4;                 // waves of a workgroup, side by side
+constexpr int kLossCols = kLossWaves * 64;    // columns of a workgroup
 constexpr int kMaxRadius = 7;
+constexpr int kLossFill = 256;  // workgroups a launch should have at least, one per CU (800x800: 51 us, 55 at 512)
 
 struct LossConst {
-    int32_t w, h, r, tiles_x;
+    int64_t cols;                // 3 w
+    int32_t w, h, band, strips;  // rows per band; workgroups across
+    int32_t want_grad;
     float lambda;
     float g[2 * kMaxRadius + 1];  // normalised 1-D window (the 2-D window is its outer product)
 };
 
-// LDS patch of the tile plus a halo of r on every side; values outside the image are 0.
-__device__ inline float ld_px(const float *__restrict__ img, int x, int y, int ch, const LossConst &L)
+// orders a wave's LDS accesses (its own lanes' stores before its loads, and those before the next stores)
+__device__ inline void wave_lds_fence()
 {
-    return (x >= 0 && x < L.w && y >= 0 && y < L.h) ? img[(int64_t(y) * L.w + x) * 3 + ch] : 0.0f;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
-__global__ __launch_bounds__(256) void k_ssim_maps(const float *__restrict__ img, const float *__restrict__ tgt,
-                                                   float *__restrict__ efg, float *__restrict__ partial,
-                                                   const LossConst L)
+template <int R>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(R > 6 ? 3 : 4))) void k_ssim_maps(
+    const float *__restrict__ img, const float *__restrict__ tgt, float *__restrict__ efg, float *__restrict__ partial,
+    const LossConst L)
 {
-    constexpr int PW = kLossTw + 2 * kMaxRadius, PH = kLossTh + 2 * kMaxRadius;
-    __shared__ float pi[PH][PW], pt[PH][PW];
-    __shared__ float hs[5][PH][kLossTw];  // horizontal window sums of I, I^, I^2, I^^2, I I^
-    __shared__ float red[2][256];
-    const int tid = threadIdx.x;
-    const int tx0 = (blockIdx.x % L.tiles_x) * kLossTw, ty0 = (blockIdx.x / L.tiles_x) * kLossTh;
-    const int r = L.r;
-    const int pw = kLossTw + 2 * r, ph = kLossTh + 2 * r;
-    const int ox = tid % kLossTw, oy = tid / kLossTw;
-    const int gx = tx0 + ox, gy = ty0 + oy;
-    const bool inside = gx < L.w && gy < L.h;
-    float ssim_sum[3], sq_sum[3];
-    for (int ch = 0; ch < 3; ++ch) {
-        __syncthreads();
-        for (int k = tid; k < pw * ph; k += 256) {
-            const int px = k % pw, py = k / pw;
-            pi[py][px] = ld_px(img, tx0 - r + px, ty0 - r + py, ch, L);
-            pt[py][px] = ld_px(tgt, tx0 - r + px, ty0 - r + py, ch, L);
-        }
-        __syncthreads();
-        for (int k = tid; k < ph * kLossTw; k += 256) {
-            const int py = k / kLossTw, px = k % kLossTw;
-            float a = 0.0f, b = 0.0f, aa = 0.0f, bb = 0.0f, ab = 0.0f;
-            for (int m = 0; m <= 2 * r; ++m) {
-                const float wv = L.g[m], x = pi[py][px + m], y = pt[py][px + m];
-                a = __builtin_fmaf(wv, x, a);
-                b = __builtin_fmaf(wv, y, b);
-                aa = __builtin_fmaf(wv, x * x, aa);
-                bb = __builtin_fmaf(wv, y * y, bb);
-                ab = __builtin_fmaf(wv, x * y, ab);
+    constexpr int W = 2 * R + 1, Line = 64 + 6 * R;
+    __shared__ float4 line4[kLossWaves][Line];  // I, I^, I^2, I^^2
+    __shared__ float line1[kLossWaves][Line];   // I I^
+    __shared__ double red[kLossWaves][6];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t c0 = int64_t(blockIdx.x % L.strips) * kLossCols + wave * 64;
+    const int y0 = (blockIdx.x / L.strips) * L.band;
+    const int rows = min(L.band, L.h - y0);
+    const int64_t c = c0 + lane;
+    // the line's columns c0 - 3 R + lane and, for the last 6 R, + 64; values outside the image are 0
+    const int64_t ca = c0 - 3 * R + lane, cb = ca + 64;
+    const bool in_a = ca >= 0 && ca < L.cols, in_b = lane < 6 * R && cb < L.cols && cb >= 0;
+    const int64_t plane = L.cols * L.h;
+    float acc[5][W], ci[W], ct[W];
+    double ssim = 0.0, sq = 0.0;
+    float ia = 0.0f, ta = 0.0f, ib = 0.0f, tb = 0.0f;
+    auto fetch = [&](int i) {
+        const int y = y0 - R + i;
+        const bool in = y >= 0 && y < L.h;
+        const int64_t at = int64_t(y) * L.cols;
+        ia = in && in_a ? img[at + ca] : 0.0f;
+        ta = in && in_a ? tgt[at + ca] : 0.0f;
+        ib = in && in_b ? img[at + cb] : 0.0f;
+        tb = in && in_b ? tgt[at + cb] : 0.0f;
+    };
+    const int n_in = rows + 2 * R;
+    if (c0 < L.cols) {
+        fetch(0);
+        for (int base = 0; base < n_in; base += W) {
+#pragma unroll
+            for (int k = 0; k < W; ++k) {
+                const int i = base + k;
+                if (i >= n_in) break;
+                line4[wave][lane] = make_float4(ia, ta, ia * ia, ta * ta);
+                line1[wave][lane] = ia * ta;
+                if (lane < 6 * R) {
+                    line4[wave][64 + lane] = make_float4(ib, tb, ib * ib, tb * tb);
+                    line1[wave][64 + lane] = ib * tb;
+                }
+                fetch(i + 1 < n_in ? i + 1 : i);
+                wave_lds_fence();
+                float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f, s4 = 0.0f;
+#pragma unroll
+                for (int m = 0; m < W; ++m) {
+                    const float4 v = line4[wave][lane + 3 * m];
+                    const float p = line1[wave][lane + 3 * m];
+                    if (m == R) {
+                        ci[k] = v.x;
+                        ct[k] = v.y;
+                    }
+                    s0 = __builtin_fmaf(L.g[m], v.x, s0);
+                    s1 = __builtin_fmaf(L.g[m], v.y, s1);
+                    s2 = __builtin_fmaf(L.g[m], v.z, s2);
+                    s3 = __builtin_fmaf(L.g[m], v.w, s3);
+                    s4 = __builtin_fmaf(L.g[m], p, s4);
+                }
+                wave_lds_fence();
+#pragma unroll
+                for (int m = 0; m < W; ++m) {
+                    const int o = (k - m + W) % W;  // the output row that this row is tap m of
+                    acc[0][o] = __builtin_fmaf(L.g[m], s0, m ? acc[0][o] : 0.0f);
+                    acc[1][o] = __builtin_fmaf(L.g[m], s1, m ? acc[1][o] : 0.0f);
+                    acc[2][o] = __builtin_fmaf(L.g[m], s2, m ? acc[2][o] : 0.0f);
+                    acc[3][o] = __builtin_fmaf(L.g[m], s3, m ? acc[3][o] : 0.0f);
+                    acc[4][o] = __builtin_fmaf(L.g[m], s4, m ? acc[4][o] : 0.0f);
+                }
+                if (i < 2 * R) continue;
+                const int o = (k + 1) % W, centre = (k - R + W) % W;
+                const float mu = acc[0][o], mh = acc[1][o], eaa = acc[2][o], ebb = acc[3][o], eab = acc[4][o];
+                const float c1 = 1e-4f, c2 = 9e-4f;
+                const float A = 2.0f * mu * mh + c1;
+                const float B = 2.0f * (eab - mu * mh) + c2;
+                const float C = mu * mu + mh * mh + c1;
+                const float D = (eaa - mu * mu) + (ebb - mh * mh) + c2;
+                const float inv = 1.0f / (C * D);
+                const float S = A * B * inv;
+                const float d = ci[centre] - ct[centre];
+                if (c < L.cols) {
+                    ssim += double(S);
+                    sq += double(d * d);
+                    if (L.want_grad) {
+                        // App. A.7: E, F, G (factored through 1 / (C D) to stay in range)
+                        const int64_t px = int64_t(y0 + i - 2 * R) * L.cols + c;
+                        efg[px] = 2.0f * inv * (mh * (B - A) - S * mu * (D - C));
+                        efg[plane + px] = 2.0f * A * inv;
+                        efg[2 * plane + px] = 2.0f * S / D;
+                    }
+                }
             }
-            hs[0][py][px] = a;
-            hs[1][py][px] = b;
-            hs[2][py][px] = aa;
-            hs[3][py][px] = bb;
-            hs[4][py][px] = ab;
         }
-        __syncthreads();
-        float s = 0.0f, q = 0.0f;
-        if (inside) {
-            float mu = 0.0f, mh = 0.0f, eaa = 0.0f, ebb = 0.0f, eab = 0.0f;
-            for (int m = 0; m <= 2 * r; ++m) {
-                const float wv = L.g[m];
-                mu = __builtin_fmaf(wv, hs[0][oy + m][ox], mu);
-                mh = __builtin_fmaf(wv, hs[1][oy + m][ox], mh);
-                eaa = __builtin_fmaf(wv, hs[2][oy + m][ox], eaa);
-                ebb = __builtin_fmaf(wv, hs[3][oy + m][ox], ebb);
-                eab = __builtin_fmaf(wv, hs[4][oy + m][ox], eab);
-            }
-            const float c1 = 1e-4f, c2 = 9e-4f;
-            const float A = 2.0f * mu * mh + c1;
-            const float B = 2.0f * (eab - mu * mh) + c2;
-            const float C = mu * mu + mh * mh + c1;
-            const float D = (eaa - mu * mu) + (ebb - mh * mh) + c2;
-            const float inv = 1.0f / (C * D);
-            const float S = A * B * inv;
-            s = S;
-            const float d = pi[oy + r][ox + r] - pt[oy + r][ox + r];
-            q = d * d;
-            // App. A.7: E, F, G (factored through 1 / (C D) to stay in range)
-            const float E = 2.0f * inv * (mh * (B - A) - S * mu * (D - C));
-            const float F = 2.0f * A * inv;
-            const float G = 2.0f * S / D;
-            const int64_t plane = int64_t(L.w) * L.h, pix = int64_t(gy) * L.w + gx;
-            efg[(3 * ch + 0) * plane + pix] = E;
-            efg[(3 * ch + 1) * plane + pix] = F;
-            efg[(3 * ch + 2) * plane + pix] = G;
-        }
-        ssim_sum[ch] = s;
-        sq_sum[ch] = q;
     }
-    // per-tile sums of the SSIM map and the squared error, per channel
+    // sums of the SSIM map and the squared error over the workgroup's columns and rows, per channel
+    const int mine = int(c % 3);
     for (int ch = 0; ch < 3; ++ch) {
-        __syncthreads();
-        red[0][tid] = ssim_sum[ch];
-        red[1][tid] = sq_sum[ch];
-        __syncthreads();
-        for (int step = 128; step > 0; step >>= 1) {
-            if (tid < step) {
-                red[0][tid] += red[0][tid + step];
-                red[1][tid] += red[1][tid + step];
-            }
-            __syncthreads();
+        double a = mine == ch ? ssim : 0.0, q = mine == ch ? sq : 0.0;
+        for (int d = 32; d > 0; d >>= 1) {
+            a += __shfl_xor(a, d);
+            q += __shfl_xor(q, d);
         }
-        if (tid == 0) {
-            partial[6 * int64_t(blockIdx.x) + ch] = red[0][0];
-            partial[6 * int64_t(blockIdx.x) + 3 + ch] = red[1][0];
+        if (lane == 0) {
+            red[wave][ch] = a;
+            red[wave][3 + ch] = q;
         }
+    }
+    __syncthreads();
+    if (threadIdx.x < 6) {
+        double a = 0.0;
+        for (int k = 0; k < kLossWaves; ++k) a += red[k][threadIdx.x];
+        partial[6 * int64_t(blockIdx.x) + threadIdx.x] = float(a);
     }
 }
 
-__global__ __launch_bounds__(256) void k_ssim_grad(const float *__restrict__ img, const float *__restrict__ tgt,
-                                                   const float *__restrict__ efg, float *__restrict__ grad,
-                                                   const LossConst L)
+template <int R>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_ssim_grad(
+    const float *__restrict__ img, const float *__restrict__ tgt, const float *__restrict__ efg, float *__restrict__ grad,
+    const LossConst L)
 {
-    constexpr int PW = kLossTw + 2 * kMaxRadius, PH = kLossTh + 2 * kMaxRadius;
-    __shared__ float pm[3][PH][PW];
-    __shared__ float hs[3][PH][kLossTw];
-    const int tid = threadIdx.x;
-    const int tx0 = (blockIdx.x % L.tiles_x) * kLossTw, ty0 = (blockIdx.x / L.tiles_x) * kLossTh;
-    const int r = L.r;
-    const int pw = kLossTw + 2 * r, ph = kLossTh + 2 * r;
-    const int ox = tid % kLossTw, oy = tid / kLossTw;
-    const int gx = tx0 + ox, gy = ty0 + oy;
-    const bool inside = gx < L.w && gy < L.h;
-    const int64_t plane = int64_t(L.w) * L.h;
-    const float inv_n = 1.0f / float(plane);
-    for (int ch = 0; ch < 3; ++ch) {
-        __syncthreads();
-        for (int k = tid; k < pw * ph; k += 256) {
-            const int px = k % pw, py = k / pw;
-            const int x = tx0 - r + px, y = ty0 - r + py;
-            const bool in = x >= 0 && x < L.w && y >= 0 && y < L.h;
-            const int64_t pix = int64_t(y) * L.w + x;
-            for (int q = 0; q < 3; ++q) pm[q][py][px] = in ? efg[(3 * ch + q) * plane + pix] : 0.0f;
-        }
-        __syncthreads();
-        for (int k = tid; k < ph * kLossTw; k += 256) {
-            const int py = k / kLossTw, px = k % kLossTw;
-            float e = 0.0f, f = 0.0f, g = 0.0f;
-            for (int m = 0; m <= 2 * r; ++m) {
-                const float wv = L.g[m];
-                e = __builtin_fmaf(wv, pm[0][py][px + m], e);
-                f = __builtin_fmaf(wv, pm[1][py][px + m], f);
-                g = __builtin_fmaf(wv, pm[2][py][px + m], g);
+    constexpr int W = 2 * R + 1, Line = 64 + 6 * R;
+    __shared__ float2 line2[kLossWaves][Line];  // E, F
+    __shared__ float line1[kLossWaves][Line];   // G
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t c0 = int64_t(blockIdx.x % L.strips) * kLossCols + wave * 64;
+    const int y0 = (blockIdx.x / L.strips) * L.band;
+    if (c0 >= L.cols) return;
+    const int rows = min(L.band, L.h - y0);
+    const int64_t c = c0 + lane;
+    const int64_t ca = c0 - 3 * R + lane, cb = ca + 64;
+    const bool in_a = ca >= 0 && ca < L.cols, in_b = lane < 6 * R && cb < L.cols && cb >= 0;
+    const int64_t plane = L.cols * L.h;
+    const float inv_n = 1.0f / float(int64_t(L.w) * L.h);
+    float acc[3][W];
+    float ea = 0.0f, fa = 0.0f, ga = 0.0f, eb = 0.0f, fb = 0.0f, gb = 0.0f, I = 0.0f, T = 0.0f;
+    auto fetch = [&](int i) {
+        const int y = y0 - R + i;
+        const bool in = y >= 0 && y < L.h;
+        const int64_t at = int64_t(y) * L.cols;
+        ea = in && in_a ? efg[at + ca] : 0.0f;
+        fa = in && in_a ? efg[plane + at + ca] : 0.0f;
+        ga = in && in_a ? efg[2 * plane + at + ca] : 0.0f;
+        eb = in && in_b ? efg[at + cb] : 0.0f;
+        fb = in && in_b ? efg[plane + at + cb] : 0.0f;
+        gb = in && in_b ? efg[2 * plane + at + cb] : 0.0f;
+        // the output row that this input row completes
+        const bool out = i >= 2 * R && c < L.cols;
+        const int64_t px = int64_t(y0 + i - 2 * R) * L.cols + c;
+        I = out ? img[px] : 0.0f;
+        T = out ? tgt[px] : 0.0f;
+    };
+    const int n_in = rows + 2 * R;
+    fetch(0);
+    for (int base = 0; base < n_in; base += W) {
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+            const int i = base + k;
+            if (i >= n_in) break;
+            line2[wave][lane] = make_float2(ea, fa);
+            line1[wave][lane] = ga;
+            if (lane < 6 * R) {
+                line2[wave][64 + lane] = make_float2(eb, fb);
+                line1[wave][64 + lane] = gb;
             }
-            hs[0][py][px] = e;
-            hs[1][py][px] = f;
-            hs[2][py][px] = g;
-        }
-        __syncthreads();
-        if (inside) {
-            float e = 0.0f, f = 0.0f, g = 0.0f;
-            for (int m = 0; m <= 2 * r; ++m) {
-                const float wv = L.g[m];
-                e = __builtin_fmaf(wv, hs[0][oy + m][ox], e);
-                f = __builtin_fmaf(wv, hs[1][oy + m][ox], f);
-                g = __builtin_fmaf(wv, hs[2][oy + m][ox], g);
+            const float Io = I, To = T;
+            fetch(i + 1 < n_in ? i + 1 : i);
+            wave_lds_fence();
+            float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
+#pragma unroll
+            for (int m = 0; m < W; ++m) {
+                const float2 v = line2[wave][lane + 3 * m];
+                s0 = __builtin_fmaf(L.g[m], v.x, s0);
+                s1 = __builtin_fmaf(L.g[m], v.y, s1);
+                s2 = __builtin_fmaf(L.g[m], line1[wave][lane + 3 * m], s2);
             }
-            const int64_t at = (int64_t(gy) * L.w + gx) * 3 + ch;
-            const float I = img[at], T = tgt[at];
-            const float dssim = (e + T * f - I * g) * inv_n;
-            grad[at] = (2.0f * (1.0f - L.lambda) * inv_n * (I - T) - 0.5f * L.lambda * dssim) * (1.0f / 3.0f);
+            wave_lds_fence();
+#pragma unroll
+            for (int m = 0; m < W; ++m) {
+                const int o = (k - m + W) % W;
+                acc[0][o] = __builtin_fmaf(L.g[m], s0, m ? acc[0][o] : 0.0f);
+                acc[1][o] = __builtin_fmaf(L.g[m], s1, m ? acc[1][o] : 0.0f);
+                acc[2][o] = __builtin_fmaf(L.g[m], s2, m ? acc[2][o] : 0.0f);
+            }
+            if (i < 2 * R || c >= L.cols) continue;
+            const int o = (k + 1) % W;
+            const float dssim = (acc[0][o] + To * acc[1][o] - Io * acc[2][o]) * inv_n;
+            grad[int64_t(y0 + i - 2 * R) * L.cols + c] =
+                (2.0f * (1.0f - L.lambda) * inv_n * (Io - To) - 0.5f * L.lambda * dssim) * (1.0f / 3.0f);
         }
     }
 }
@@ -208,27 +263,30 @@ __global__ __launch_bounds__(256) void k_loss_total(const float *__restrict__ pa
 
 // ------------------------------------------------------------------- host
 
-static LossConst loss_const(int32_t w, int32_t h, const rs_loss_params *lp)
+static LossConst loss_const(int32_t w, int32_t h, const rs_loss_params *lp, bool grad)
 {
+    const int r = lp->radius;
     LossConst L{};
     L.w = w;
     L.h = h;
-    L.r = lp->radius;
-    L.tiles_x = (w + kLossTw - 1) / kLossTw;
+    L.cols = 3 * int64_t(w);
+    L.strips = int((L.cols + kLossCols - 1) / kLossCols);
+    L.want_grad = grad;
+    // Rows per band: a band re-reads 2 r rows, and a launch needs some waves on every SIMD.
+    L.band = 32;
+    while (L.band > 8 && int64_t(L.strips) * ((h + L.band - 1) / L.band) < kLossFill) L.band /= 2;
     L.lambda = lp->lambda;
     double g[2 * kMaxRadius + 1], sum = 0.0;
-    for (int m = -L.r; m <= L.r; ++m) {
-        g[m + L.r] = exp(-double(m) * m / (2.0 * double(lp->sigma) * lp->sigma));
-        sum += g[m + L.r];
+    for (int m = -r; m <= r; ++m) {
+        g[m + r] = exp(-double(m) * m / (2.0 * double(lp->sigma) * lp->sigma));
+        sum += g[m + r];
     }
-    for (int m = 0; m <= 2 * L.r; ++m) L.g[m] = float(g[m] / sum);
+    for (int m = 0; m <= 2 * r; ++m) L.g[m] = float(g[m] / sum);
     return L;
 }
 
-static int64_t loss_tiles(int32_t w, int32_t h)
-{
-    return int64_t((w + kLossTw - 1) / kLossTw) * ((h + kLossTh - 1) / kLossTh);
-}
+// room for the partial sums: 32 x 8 pixels per set, no more than a workgroup's columns and a shortest band
+static int64_t loss_tiles(int32_t w, int32_t h) { return int64_t((w + 31) / 32) * ((h + 7) / 8); }
 
 size_t loss_workspace_bytes(int32_t w, int32_t h)
 {
@@ -236,17 +294,33 @@ size_t loss_workspace_bytes(int32_t w, int32_t h)
     return maps + align256(size_t(loss_tiles(w, h)) * 6 * 4);
 }
 
+template <int R>
+static void launch_ssim(const float *img, const float *tgt, float *efg, float *partial, float *grad, int blocks,
+                        const LossConst &L, hipStream_t st)
+{
+    k_ssim_maps<R><<<blocks, 256, 0, st>>>(img, tgt, efg, partial, L);
+    if (grad) k_ssim_grad<R><<<blocks, 256, 0, st>>>(img, tgt, efg, grad, L);
+}
+
 int launch_loss(const float *img, const float *tgt, int32_t w, int32_t h, const rs_loss_params *lp, float *loss,
                 float *grad, void *ws, hipStream_t st)
 {
-    const LossConst L = loss_const(w, h, lp);
-    const int64_t tiles = loss_tiles(w, h);
+    const LossConst L = loss_const(w, h, lp, grad != nullptr);
+    const int64_t blocks = int64_t(L.strips) * ((h + L.band - 1) / L.band);
     float *efg = static_cast<float *>(ws);
     float *partial = reinterpret_cast<float *>(static_cast<char *>(ws) +
                                                align256(size_t(9) * size_t(w) * size_t(h) * 4));
-    k_ssim_maps<<<int(tiles), 256, 0, st>>>(img, tgt, efg, partial, L);
-    if (grad) k_ssim_grad<<<int(tiles), 256, 0, st>>>(img, tgt, efg, grad, L);
-    k_loss_total<<<1, 256, 0, st>>>(partial, tiles, loss, L);
+    switch (lp->radius) {
+    case 1: launch_ssim<1>(img, tgt, efg, partial, grad, int(blocks), L, st); break;
+    case 2: launch_ssim<2>(img, tgt, efg, partial, grad, int(blocks), L, st); break;
+    case 3: launch_ssim<3>(img, tgt, efg, partial, grad, int(blocks), L, st); break;
+    case 4: launch_ssim<4>(img, tgt, efg, partial, grad, int(blocks), L, st); break;
+    case 5: launch_ssim<5>(img, tgt, efg, partial, grad, int(blocks), L, st); break;
+    case 6: launch_ssim<6>(img, tgt, efg, partial, grad, int(blocks), L, st); break;
+    case 7: launch_ssim<7>(img, tgt, efg, partial, grad, int(blocks), L, st); break;
+    default: return RS_ERR_INVALID_ARG;
+    }
+    k_loss_total<<<1, 256, 0, st>>>(partial, blocks, loss, L);
     return hipGetLastError() == hipSuccess ? RS_OK : RS_ERR_HIP;
 }
 
