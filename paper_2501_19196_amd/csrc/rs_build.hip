@@ -37,6 +37,8 @@ __global__ void k_fill_u32(uint32_t *p, int64_t n, uint32_t v)
 
 // ------------------------------------------------------------- scene bounds
 
+// Bound by atomics to six words unless each wave reduces its own first and few workgroups add theirs (1M points:
+// 13 us; 28 with 1024 workgroups, 38 with an LDS atomic per thread and axis as well).
 __global__ __launch_bounds__(256) void k_bounds(const float *__restrict__ mean, int64_t n, WsHeader *h)
 {
     __shared__ uint32_t lo[3], hi[3];
@@ -55,8 +57,14 @@ __global__ __launch_bounds__(256) void k_bounds(const float *__restrict__ mean, 
         }
     }
     for (int k = 0; k < 3; ++k) {
-        atomicMin(&lo[k], l[k]);
-        atomicMax(&hi[k], u[k]);
+        for (int d = kWave / 2; d > 0; d >>= 1) {
+            l[k] = min(l[k], uint32_t(__shfl_xor(int(l[k]), d)));
+            u[k] = max(u[k], uint32_t(__shfl_xor(int(u[k]), d)));
+        }
+        if ((threadIdx.x & (kWave - 1)) == 0) {
+            atomicMin(&lo[k], l[k]);
+            atomicMax(&hi[k], u[k]);
+        }
     }
     __syncthreads();
     if (threadIdx.x < 3) {
@@ -251,50 +259,49 @@ __global__ __launch_bounds__(kSortBlock) void k_sort_hist(const uint32_t *__rest
     hist[int64_t(threadIdx.x) * nblocks + blockIdx.x] = hs[threadIdx.x];
 }
 
+// Exclusive scan over a workgroup of 256 threads; ws holds an int per wave. `total` is the sum.
+__device__ inline uint32_t scan256(uint32_t v, uint32_t &total, uint32_t *ws)
+{
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    uint32_t x = v;
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        const uint32_t y = uint32_t(__shfl_up(int(x), d));
+        if (lane >= d) x += y;
+    }
+    if (lane == kWave - 1) ws[wave] = x;
+    __syncthreads();
+    uint32_t before = 0;
+    total = 0;
+#pragma unroll
+    for (int w = 0; w < 256 / kWave; ++w) {
+        before += w < wave ? ws[w] : 0u;
+        total += ws[w];
+    }
+    return before + x - v;
+}
+
 // Exclusive scan of the digit-major histogram in two steps: each workgroup
-// scans one digit's row over the tiles and records the row total, then one
-// workgroup scans the 256 totals into digit bases.
+// scans one digit's row over the tiles and records the row total; the scatter
+// scans the 256 totals into digit bases itself.
 __global__ __launch_bounds__(256) void k_sort_scan_rows(uint32_t *__restrict__ hist, int64_t nblocks,
                                                         uint32_t *__restrict__ totals)
 {
-    __shared__ uint32_t s[256];
+    __shared__ uint32_t s[256 / kWave];
     const int t = threadIdx.x;
     uint32_t *row = hist + int64_t(blockIdx.x) * nblocks;
     const int64_t per = (nblocks + 255) / 256;
     const int64_t b = t * per, e = min(b + per, nblocks);
     uint32_t sum = 0;
     for (int64_t i = b; i < e; ++i) sum += row[i];
-    s[t] = sum;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        uint32_t v = t >= off ? s[t - off] : 0u;
-        __syncthreads();
-        s[t] += v;
-        __syncthreads();
-    }
-    uint32_t run = s[t] - sum;
+    uint32_t total;
+    uint32_t run = scan256(sum, total, s);
     for (int64_t i = b; i < e; ++i) {
         uint32_t v = row[i];
         row[i] = run;
         run += v;
     }
-    if (t == 255) totals[blockIdx.x] = s[255];
-}
-
-__global__ __launch_bounds__(256) void k_sort_scan_bases(uint32_t *__restrict__ totals)
-{
-    __shared__ uint32_t s[256];
-    const int t = threadIdx.x;
-    const uint32_t mine = totals[t];
-    s[t] = mine;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        uint32_t v = t >= off ? s[t - off] : 0u;
-        __syncthreads();
-        s[t] += v;
-        __syncthreads();
-    }
-    totals[256 + t] = s[t] - mine;  // exclusive base of digit t
+    if (t == 255) totals[blockIdx.x] = total;
 }
 
 // Stable scatter: within a tile, keys are ranked among equal digits in input
@@ -304,12 +311,15 @@ __global__ __launch_bounds__(kSortBlock) void k_sort_scatter(const uint32_t *__r
                                                              const uint32_t *__restrict__ vin,
                                                              uint32_t *__restrict__ kout, uint32_t *__restrict__ vout,
                                                              int64_t n, int shift, const uint32_t *__restrict__ hist,
-                                                             int64_t nblocks, const uint32_t *__restrict__ bases)
+                                                             int64_t nblocks, const uint32_t *__restrict__ totals)
 {
     __shared__ uint32_t run[256];
     __shared__ uint32_t wcount[kSortBlock / kWave][256];
     const int t = threadIdx.x, w = t / kWave, lane = t % kWave;
-    run[t] = bases[t] + hist[int64_t(t) * nblocks + blockIdx.x];
+    __shared__ uint32_t scan_ws[kSortBlock / kWave];
+    static_assert(kSortBlock == 256, "a thread per digit");
+    uint32_t all;
+    run[t] = scan256(totals[t], all, scan_ws) + hist[int64_t(t) * nblocks + blockIdx.x];
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     int64_t base = int64_t(blockIdx.x) * kSortTile;
     for (int c = 0; c < kSortItems; ++c) {
@@ -1150,7 +1160,7 @@ static int build_core(int64_t n, const float *points, const float *scale, const 
         else
             k_small_sort<4><<<1, kSmallThreads, 0, st>>>(points, scale, quat, opacity, rgb, int(n), init_header, h, codes, vals);
     } else {
-        k_bounds<<<bgrid < 1024 ? bgrid : 1024, 256, 0, st>>>(points, n, h);
+        k_bounds<<<bgrid < 256 ? bgrid : 256, 256, 0, st>>>(points, n, h);
         k_morton<<<bgrid, 256, 0, st>>>(points, scale, quat, opacity, rgb, n, h, codes, vals);
         // 4 passes of 8 bits: A -> B -> A -> B -> A
         uint32_t *ka = codes, *va = vals, *kb = kalt, *vb = valt;
@@ -1159,8 +1169,7 @@ static int build_core(int64_t n, const float *points, const float *scale, const 
             int shift = 8 * pass;
             k_sort_hist<<<int(nb), kSortBlock, 0, st>>>(ka, n, shift, hist, nb);
             k_sort_scan_rows<<<256, 256, 0, st>>>(hist, nb, totals);
-            k_sort_scan_bases<<<1, 256, 0, st>>>(totals);
-            k_sort_scatter<<<int(nb), kSortBlock, 0, st>>>(ka, va, kb, vb, n, shift, hist, nb, totals + 256);
+            k_sort_scatter<<<int(nb), kSortBlock, 0, st>>>(ka, va, kb, vb, n, shift, hist, nb, totals);
             uint32_t *t;
             t = ka; ka = kb; kb = t;
             t = va; va = vb; vb = t;
