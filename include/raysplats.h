@@ -114,18 +114,23 @@ typedef struct {
 
 /* Renderer knobs. Q: ellipsoid quantile (Sec. 3; > 0). eps1: transmittance
  * threshold (>= 0). t_min: minimum hit depth (finite, >= 0). max_hits: K_max (0 = unbounded).
- * kbuf: hits gathered per ray per traversal round (8, 16, 24, 32 or 48; 0 = 48,
- * the size rs_autotune picks for the forward on every measured workload; the
- * result does not depend on it).
- * stack_depth: traversal stack entries (1..64; 0 = 64). tile_width: width in
- * pixels of the 64-ray packet tile of a view (4, 8, 16 or 32, i.e. 4x16, 8x8,
- * 16x4 or 32x2 pixels; 0 = 8); like kbuf it changes the time, not the result.
+ * kbuf: hits a ray's buffer holds (8, 16, 24, 32 or 48; 0 = automatic; the
+ * result does not depend on it). The traversal adjoint and forward calls that
+ * walk take it as it is (0 = 48); the frontier forward has buffers of 16, 24
+ * and 32 hits and takes the smallest that holds kbuf, or its largest (0 = 24).
+ * stack_depth: traversal stack entries (1..64; 0 = automatic: the walks take
+ * 64; a forward call that names a depth walks the BVH depth first).
+ * tile_width: width in pixels of the 64-ray packet tile of a view (4, 8, 16 or
+ * 32, i.e. 4x16, 8x8, 16x4 or 32x2 pixels; 0 = 8); like kbuf it changes the
+ * time, not the result. Launches of few rays, or over small views of large
+ * scenes, trace packets of 16 rays (4x4 pixels), or 4 (2x2) without lists,
+ * and leave tile_width aside.
  * hit_list: store-or-recompute choice of the adjoint (0..4096; 0 = recompute):
  * with C > 0 the forward also records the ids of the Gaussians each ray
  * composites, in a pool of C 4-byte slots per ray on average inside the ray
- * state (per compositing step of its wavefront a packet of 64 rays stores one
+ * state (per compositing step of its wavefront a packet stores one
  * row: the ids of the lanes that took a hit at that step and their 64-bit lane
- * mask, in chunks of 512 slots), and the adjoint replays those lists
+ * mask, in chunks of 8 slots per ray of a packet), and the adjoint replays those lists
  * instead of traversing the BVH again. The rays of a packet that finds the pool
  * exhausted are traversed again by the adjoint. The gradients are the same (up to
  * float atomic order). The mesh renders keep one pool for all their ray sets in
@@ -167,7 +172,7 @@ size_t rs_bvh_workspace_bytes(int64_t n_gaussians);
  * 16 bytes per ray that the adjoint starts from (the last composited hit and
  * where T reached 0) and, when p->hit_list = C > 0, 16 bytes of list
  * bookkeeping per ray plus the stored-list pool (C slots of 4 bytes per ray on
- * average, in whole chunks of 2 KiB, after a 256-byte header). */
+ * average, in whole units of 2 KiB, after a 256-byte header). */
 size_t rs_ray_state_bytes(int64_t n_rays, const rs_params *p);
 
 /* Build the BVH: 30-bit Morton codes of the means, LDS radix sort, leaf boxes
@@ -216,8 +221,9 @@ int rs_read_status(const rs_bvh *bvh, void *stream);
 
 /* Synchronise `stream` and copy the work counters accumulated by render calls
  * made with RS_COUNTERS since the last rs_build_bvh (host uint64 out[16]):
- * [0] forward ray packets, [1] inner-node visits, [2] leaf visits, [3]
- * traversal rounds (all per wavefront), [4] lane leaf tests on live rays, [5]
+ * [0] forward ray packets, [1] inner-node visits (frontier forward: nodes
+ * expanded), [2] leaf visits (leaves tested ray by ray), [3] traversal rounds
+ * (all per wavefront), [4] lane leaf tests on live rays, [5]
  * hits entering a lane's buffer, [6] forward: hits consumed (composited, or
  * collected by the paper variant), traversal adjoint: hits differentiated, [7]
  * lane child-box overlaps, [8] traversal adjoint: accumulator lines flushed

@@ -480,7 +480,7 @@ int rs_bvh_download(const rs_bvh *bvh, uint32_t *codes, int32_t *perm, int32_t *
     return RS_OK;
 }
 
-// Lane of ray r inside its 64-ray packet (the tile layout of rs_render_fwd).
+// Lane of ray r inside its packet (the tile layout of rs_render_fwd).
 static int ray_lane(const rs_rays *rays, int tile_shift, int pkt_shift, int64_t r)
 {
     if (rays->n_views == 0) return int(r & ((1 << pkt_shift) - 1));

@@ -1,18 +1,21 @@
 // Ray-packet traversal, ellipsoid intersection, depth-ordered compositing and
 // its adjoint, for gfx950 (wave64).
 //
-// One wavefront traces one packet of 64 rays (an 8x8 pixel tile). The whole
-// wave walks the BVH together: node and Gaussian records are fetched once per
-// wave (uniform addresses, scalar loads) and every lane tests them against its
-// own ray; a child is entered when any lane's ray overlaps it (ballot). The
-// traversal stack is wave-uniform and lives in one VGPR (entry k in lane k).
+// One wavefront traces one packet of 64 rays (an 8x8 pixel tile; 16 or 4 rays in small launches).
+// Each lane keeps its nearest not-yet-composited hits, ordered by the key (t1, Gaussian index), in
+// registers, and composites them front to back (Eq. 3) with the K_max and eps1 stops (Sec. 3, "Color
+// Aggregation"). There are two ways to find them, with the same result bit for bit:
 //
-// Each lane keeps its K nearest not-yet-composited hits, ordered by the key
-// (t1, Gaussian index), in registers. A round traverses the BVH collecting
-// the K smallest keys above the previous round's last key (nodes are culled
-// against [last t, K-th t]), then composites them front to back (Eq. 3) with
-// the K_max and eps1 stops (Sec. 3, "Color Aggregation"). Rounds repeat
-// until every lane has stopped or run out of hits.
+// The frontier kernel (k_render_front, most forward calls) lets the lanes test 64 nodes, then 64
+// leaves, at a time against the bundle of the packet's rays, from near to far, and tests the
+// leaves that survive ray by ray; hits in front of all open work are composited at once.
+//
+// The walk (k_render, and the frontier kernel's fallback): the whole wave walks the BVH depth
+// first; node and Gaussian records are fetched once per wave (uniform addresses, scalar loads) and
+// every lane tests them against its own ray; a child is entered when any lane's ray overlaps it
+// (ballot). The traversal stack is wave-uniform and lives in one VGPR (entry k in lane k). A round
+// collects the K smallest keys above the previous round's last key (nodes are culled against
+// [last t, K-th t]), then composites them. Rounds repeat until every lane has stopped or run out of hits.
 //
 // The adjoint (App. A.3-A.6) walks each ray's composited hits back to front,
 // either from the forward's stored lists or by traversing the BVH again in
@@ -496,21 +499,13 @@ __device__ inline float hit_alpha_at(int32_t js, const Ray &ray, const float4 *_
     return r3.w * __expf(-0.5f * h2);
 }
 
-// the same for Gaussian gid
-__device__ inline float hit_alpha(uint32_t gid, const Ray &ray, const float4 *__restrict__ records,
-                                  const int32_t *__restrict__ inv, float Q, float4 &r0, float4 &r1, float4 &r2,
-                                  float4 &r3, float &t1, float &h2, HitGeom &G)
-{
-    return hit_alpha_at(inv[gid], ray, records, Q, r0, r1, r2, r3, t1, h2, G);
-}
-
 // alpha, colour and test intermediates of a hit (no compositing). EVERY: every lane
 // computes, the caller giving idle lanes a valid Gaussian index whose values it never
 // uses, so no lane is masked off and nothing is zeroed first.
 template <bool EVERY = false>
-__device__ inline void recompute_hit(bool act, uint32_t gid, const Ray &ray, const float4 *__restrict__ records,
-                                     const int32_t *__restrict__ inv, const float *__restrict__ rgb, bool zc, float Q,
-                                     HitData &H)
+__device__ inline void recompute_hit_at(bool act, uint32_t gid, int32_t js, const Ray &ray,
+                                        const float4 *__restrict__ records, const float *__restrict__ rgb, bool zc,
+                                        float Q, HitData &H)
 {
     H.Tk = 0.0f;
     if (!EVERY) {
@@ -518,7 +513,7 @@ __device__ inline void recompute_hit(bool act, uint32_t gid, const Ray &ray, con
         H.g = HitGeom{};
     }
     if (EVERY || act) {
-        H.al = hit_alpha(gid, ray, records, inv, Q, H.r0, H.r1, H.r2, H.r3, H.t1, H.h2, H.g);
+        H.al = hit_alpha_at(js, ray, records, Q, H.r0, H.r1, H.r2, H.r3, H.t1, H.h2, H.g);
         H.cr = H.cg = H.cb = 0.0f;
         if (!zc) {
             H.cr = rgb[3 * gid];
@@ -2119,7 +2114,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(waves_for(K,
                 if (COUNT) c_lcomp += __popcll(act_mask);
                 const uint32_t gid = hit_key_gid(nk);
                 HitData H;
-                recompute_hit(act, gid, ray, records, inv, ptr.rgb, zc, P.Q, H);
+                recompute_hit_at(act, gid, act ? inv[gid] : 0, ray, records, ptr.rgb, zc, P.Q, H);
                 const float Tk = back_T(B, H.al);
                 adjoint_hit<COUNT, true>(act, act_mask, gid, H, Tk, B, Gd, zc, ptr.gacc, lane, c_group);
                 if (act) {
@@ -2160,10 +2155,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(waves_for(K,
 // buffer. The paper variant's second-phase hits (flagged, after the composited
 // ones) only build the colour behind the last composited hit. Rays whose list is
 // incomplete are left to the traversal adjoint.
-// Six waves per SIMD hide the gathers better than five; seven and eight spill.
-#ifndef RS_LIST_WAVES
-#define RS_LIST_WAVES 6
-#endif
+// Bound by the gathers of records and the line atomics; the position lookup and the entries come one and two
+// rows ahead (1M Gaussians, 1920x1080, forward's rows of this size: 2.75 ms, 2.94 with the lookup in line).
+// Seven waves per SIMD: 2.75 ms; six 2.82, five 2.85.
+constexpr int kListWaves = 7;
 // Row cursor of the list adjoint (wave-uniform): `start` is where the row read last began,
 // so the next row (back to front) ends there, or at the fill of an earlier chunk.
 __device__ inline void row_seek(const int32_t *__restrict__ prev, const int32_t *__restrict__ fill, int32_t &chunk,
@@ -2197,7 +2192,7 @@ __device__ inline uint32_t row_entry(const uint32_t *__restrict__ slots, int32_t
 }
 
 template <bool COUNT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RS_LIST_WAVES))) void k_adjoint_list(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kListWaves))) void k_adjoint_list(
     const float4 *__restrict__ records, const int32_t *__restrict__ inv, const Ptrs ptr, const RenderParams P)
 {
     const int lane = threadIdx.x;
@@ -2232,27 +2227,33 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RS_LIST_WAVE
         int32_t chunk = __builtin_amdgcn_readfirstlane(li.z);
         if (!wave_ballot(live) || chunk < 0) continue;
         // Rows are walked from the last to the first: a row ends with its lane mask, so the
-        // mask at the row's end gives its start, which is the previous row's end. The next
-        // row's mask and this lane's entry in it are loaded while a row is processed.
+        // mask at the row's end gives its start, which is the previous row's end. While a row is
+        // processed, the next one's sorted positions and the one after that's entries are loaded, so
+        // a row waits for its records alone.
         int32_t start = fill[chunk];
         row_seek(prev, fill, chunk, start);
-        uint32_t e = kListIdle;
-        if (chunk >= 0) e = row_entry(slots, ptr.pool.chunk_slots, chunk, start, live, lane);
-        while (chunk >= 0) {
-            int32_t nchunk = chunk, nstart = start;
-            row_seek(prev, fill, nchunk, nstart);
-            uint32_t ne = kListIdle;
-            if (nchunk >= 0) ne = row_entry(slots, ptr.pool.chunk_slots, nchunk, nstart, live, lane);
-            chunk = nchunk;
-            start = nstart;
-            const uint32_t cur = e;
-            e = ne;
+        uint32_t e1 = kListIdle, e0 = kListIdle;
+        int32_t js0 = 0;
+        bool row1 = chunk >= 0, row0 = true;
+        if (row1) e1 = row_entry(slots, ptr.pool.chunk_slots, chunk, start, live, lane);
+        while (row0) {
+            const uint32_t cur = e0;
+            const int32_t js = js0;
+            e0 = e1;
+            row0 = row1;
+            js0 = inv[e0 != kListIdle ? e0 & ~kListSecond : 0u];  // idle lanes read Gaussian 0 (unused)
+            e1 = kListIdle;
+            if (row1) {
+                row_seek(prev, fill, chunk, start);
+                row1 = chunk >= 0;
+                if (row1) e1 = row_entry(slots, ptr.pool.chunk_slots, chunk, start, live, lane);
+            }
             const bool act = cur != kListIdle;
             if (!wave_ballot(act)) continue;
             const bool comp = act && cur < kListSecond;
-            const uint32_t gid = act ? cur & ~kListSecond : 0u;  // idle lanes read Gaussian 0 (unused)
+            const uint32_t gid = act ? cur & ~kListSecond : 0u;
             HitData H;
-            recompute_hit<true>(act, gid, LR.ray, records, inv, ptr.rgb, zc, P.Q, H);
+            recompute_hit_at<true>(act, gid, js, LR.ray, records, ptr.rgb, zc, P.Q, H);
             const float Tk = back_T(B, H.al);
             const uint64_t comp_mask = wave_ballot(comp);
             if (COUNT) c_lcomp += __popcll(comp_mask);
