@@ -1246,7 +1246,9 @@ __device__ inline bool walk_rounds(LaneState &S, LaneCold &C, const LaneRay &LR,
     return true;
 }
 
-// The walk as a kernel of its own: for brute force and for calls that bound the traversal stack.
+// The walk as a kernel of its own: for brute force, for calls that bound the traversal stack, and for the paper
+// variant, whose pool is sized for the walk's rows: every step consumes a hit of each live ray, so a packet stores at
+// most max_hits of them. (The frontier drains its rays at different steps: up to four times as many rows.)
 template <int K, bool BRUTE, bool COUNT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(waves_for(K, false)))) void k_render(
     const float4 *__restrict__ records, const float4 *__restrict__ nodes, const int32_t *__restrict__ gidx,
@@ -1521,8 +1523,7 @@ constexpr int64_t kFrontFew = 2048;
 constexpr int kFrontDrain = 32;  // lanes with a final hit that make a drain step worth while
 constexpr int kFrontDefault = 24;
 
-// GENERAL: with work counters and the paper variant's second phase.
-template <int K, bool GENERAL>
+template <int K, bool COUNT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_render_front(
     const float4 *__restrict__ records, const float4 *__restrict__ nodes, const int32_t *__restrict__ gidx,
     const int32_t *__restrict__ inv, const Ptrs ptr, const RenderParams P)
@@ -1537,7 +1538,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
     for (;;) {
         const int64_t pkt = next_packet(P, ptr.queue, lane, xcd, qi, iter_pkt);
         if (pkt >= P.n_packets) break;
-        if (GENERAL) ++cnt.pkt;
+        if (COUNT) ++cnt.pkt;
         LaneState S;
         bool zc, lists;
         {
@@ -1612,7 +1613,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
             int rounds = 0;
             // rounds, until the group's rays have stopped or run out of hits
             for (uint64_t on_mask = grp & wave_ballot(S.live); on_mask && !redo; on_mask = grp & wave_ballot(S.live)) {
-                if (GENERAL) ++cnt.round;
+                if (COUNT) ++cnt.round;
                 hb.clear();
                 double cap = F.stop[lane];
                 F.start[lane] = S.last;
@@ -1707,7 +1708,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                         float ln, rn;
                         const uint64_t hl = wave_ballot(box_meets(B, n0.x, n0.y, n0.z, n0.w, n1.x, n1.y, ln) && mine);
                         const uint64_t hr = wave_ballot(box_meets(B, n1.z, n1.w, n2.x, n2.y, n2.z, n2.w, rn) && mine);
-                        if (GENERAL) {
+                        if (COUNT) {
                             cnt.node += m;
                             cnt.lchild += __popcll(hl) + __popcll(hr);
                         }
@@ -1853,7 +1854,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                             const float h2a = ellipsoid_h2(S.ray, a0, a1, a2, a3, ha);
                             const float h2b = ellipsoid_h2(S.ray, b0, b1, b2, b3, hb2);
                             asm volatile("" ::"s"(ga), "s"(gb));  // the index loads are issued with the records'
-                            if (GENERAL) {
+                            if (COUNT) {
                                 cnt.leaf += i + 1 < nS ? 2 : 1;
                                 cnt.lleaf += __popcll(on_mask) * (i + 1 < nS ? 2 : 1);
                             }
@@ -1892,7 +1893,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                                                     wave_ballot(hit_key_t(key) < tf) & wave_ballot(key < cap);
                                 if (am == 0) break;
                                 if (__popcll(am) < least && (am & wave_ballot(hb.key[K - 2] != kNoHit)) == 0) break;
-                                if (GENERAL) cnt.lcomp += __popcll(am);
+                                if (COUNT) cnt.lcomp += __popcll(am);
                                 const bool act = __builtin_amdgcn_inverse_ballot_w64(am);
                                 const double key_s = key;
                                 const int32_t js_s = js;
@@ -1900,7 +1901,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                                 rejoin();
                                 key = hb.front();
                                 js = inv[key != kNoHit ? hit_key_gid(key) : 0u];
-                                consume<GENERAL>(act, key_s, js_s, S, cold, records, ptr, P, zc, lists, LC, lane);
+                                consume<false>(act, key_s, js_s, S, cold, records, ptr, P, zc, lists, LC, lane);
                             }
                             on_mask = grp & wave_ballot(S.live);
                             if (end || !on_mask) break;
@@ -1911,7 +1912,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                                 break;
                             }
                         }
-                        if (GENERAL) cnt.lbuf += __popcll(ma) + __popcll(mb);
+                        if (COUNT) cnt.lbuf += __popcll(ma) + __popcll(mb);
                         const bool ca = __builtin_amdgcn_inverse_ballot_w64(ma), cb = __builtin_amdgcn_inverse_ballot_w64(mb);
                         if (ma) cap = min_bare(cap, hb.insert_out(ca ? ka : kNoHit));
                         if (mb) cap = min_bare(cap, hb.insert_out(cb ? kb : kNoHit));
@@ -1920,7 +1921,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                         Tv *= (ca ? oma : 1.0f) * (cb ? omb : 1.0f);
                         tv = fmaxf(tv, fmaxf(ca ? ta : 0.0f, cb ? tb : 0.0f));
                         const bool closed = Tv < 0.99f * P.eps1;
-                        if ((ma | mb) & wave_ballot(closed) && !(GENERAL && P.paper)) {
+                        if ((ma | mb) & wave_ballot(closed)) {
                             const double far = __longlong_as_double(__double_as_longlong(bound_key(tv)) + (1ll << 32));
                             cap = closed ? min_bare(cap, far) : cap;
                             const float zr = wave_max(__builtin_amdgcn_inverse_ballot_w64(on_mask)
@@ -1985,17 +1986,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
             // start over with the walk; the packet's first list chunk is used again
             lane_reset(S, cold, LR.valid && P.n_gauss > 0 && LR.tmax > P.t_min, lane);
             LC = ListCursor{0, LC.first, 0, 0, LC.first, true};
-            if (!walk_rounds<HitBuf<K>, false, false, GENERAL, GENERAL>(S, cold, LR, zc, lists, LC, records, nodes, gidx, inv,
+            if (!walk_rounds<HitBuf<K>, false, false, COUNT, false>(S, cold, LR, zc, lists, LC, records, nodes, gidx, inv,
                                                                          ptr, P, hb, lane, cnt))
                 if (lane == 0) atomicOr(ptr.status, kStatusStack);
         }
         write_rays(S, cold, LR, ptr.set[LR.si], ptr, LC, lists, lane);
-        if (GENERAL) {
+        if (COUNT) {
             cnt.rows += uint64_t(LC.rows);
             cnt.slots += uint64_t(LC.slots);
         }
     }
-    if (GENERAL) add_counts(cnt, ptr, lane);
+    if (COUNT) add_counts(cnt, ptr, lane);
 }
 
 // ------------------------------------------------- adjoint by re-traversal
@@ -2366,7 +2367,7 @@ static int plain_grid(int64_t n_packets)
 template <int K>
 static void launch_front(const KernArgs &a, const Ptrs &ptr, const RenderParams &P, hipStream_t st)
 {
-    if (P.count || P.paper)
+    if (P.count)
         k_render_front<K, true><<<a.grid, kWave, 0, st>>>(a.records, a.nodes, a.gidx, a.inv, ptr, P);
     else
         k_render_front<K, false><<<a.grid, kWave, 0, st>>>(a.records, a.nodes, a.gidx, a.inv, ptr, P);
@@ -2430,10 +2431,12 @@ int launch_sets(const BvhDesc &D, const rs_gaussians *g, const rs_params *p, int
     P.persistent = (p->flags & RS_PERSISTENT) ? 1 : 0;
     P.brute = (p->flags & RS_BRUTE_FORCE) ? 1 : 0;
     P.count = (p->flags & RS_COUNTERS) ? 1 : 0;
-    // the frontier kernel keeps no stack: a call that bounds the stack takes the walk. So do the sets of paths
+    // the frontier kernel keeps no stack: a call that bounds the stack takes the walk. So does the paper variant (its
+    // pool bound, see k_render), and so do the sets of paths
     // of several bounces: refracted rays of a packet go all ways (150k Gaussians, 640x361, three bounces: 7.7 ms
     // walked, 9.2 to 22 otherwise).
-    P.front = pass == Pass::Forward && !P.brute && p->stack_depth == 0 && nsets <= 3 &&
+    const bool paper = (p->flags & RS_PAPER_GRADIENT) && room.units > 0;
+    P.front = pass == Pass::Forward && !P.brute && !paper && p->stack_depth == 0 && nsets <= 3 &&
               (D.n > kFrontFew || packet_shift(rays, nsets, p, D.n) < 6);
     const int pkt_shift = P.front && room.units == 0 ? packet_shift_no_lists(rays, nsets, p, D.n)
                                                      : packet_shift(rays, nsets, p, D.n);
@@ -2444,7 +2447,7 @@ int launch_sets(const BvhDesc &D, const rs_gaussians *g, const rs_params *p, int
     P.strip_tiles = kStripTiles;
     P.lists = pool.chunks > 0 ? 1 : 0;
     P.overflow_only = (pass == Pass::AdjointTraverse && P.lists) ? 1 : 0;
-    P.paper = (p->flags & RS_PAPER_GRADIENT) && P.lists ? 1 : 0;
+    P.paper = paper ? 1 : 0;
     P.eps2 = p->eps2;
     P.chunk = (P.n_packets + kXcdQueues - 1) / kXcdQueues;
 
