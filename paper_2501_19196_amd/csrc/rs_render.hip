@@ -784,7 +784,7 @@ struct ListCursor {
     int32_t chunk;  // current chunk (-1: none yet)
     int32_t fill;   // slots used in the current chunk
     int32_t slots;  // slots stored (rows and masks)
-    int32_t first;  // first chunk (-1: none yet)
+    int32_t spare;  // last chunk of an abandoned attempt of this packet, its chunks to be used again (-1: none)
     bool ok;        // false once the pool was found exhausted
 };
 
@@ -806,14 +806,19 @@ __device__ inline void list_append(const ListPool &pool, ListCursor &L, uint32_t
     if (m == 0) return;
     const int32_t need = __popcll(m) + 2;
     if (L.chunk < 0 || L.fill + need > pool.chunk_slots) {
-        int32_t c = 0;
+        int32_t c = L.spare, spare = -1;
         if (lane == 0) {
             if (L.chunk >= 0) pool.fill[L.chunk] = L.fill;
-            const unsigned long long k = atomicAdd(pool.hdr, 1ull);
-            c = k < (unsigned long long)pool.chunks ? int32_t(k) : -1;
+            if (c >= 0) {
+                spare = pool.prev[c];
+            } else {
+                const unsigned long long k = atomicAdd(pool.hdr, 1ull);
+                c = k < (unsigned long long)pool.chunks ? int32_t(k) : -1;
+            }
         }
         rejoin();
         c = __builtin_amdgcn_readfirstlane(c);
+        L.spare = __builtin_amdgcn_readfirstlane(spare);
         if (c < 0) {
             L.ok = false;
             if (lane == 0) {
@@ -825,7 +830,6 @@ __device__ inline void list_append(const ListPool &pool, ListCursor &L, uint32_t
         }
         if (lane == 0) pool.prev[c] = L.chunk;
         rejoin();
-        if (L.chunk < 0) L.first = c;
         L.chunk = c;
         L.fill = 0;
     }
@@ -1556,7 +1560,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
         }
         ListCursor LC{0, -1, 0, 0, -1, true};
         HitBuf<K> hb;
-        bool redo = false;
+        // A group that is better walked is left to the walk, which goes on behind the hits that its rays have
+        // consumed; only where their order was wrong does the packet start over.
+        bool leave = false, redo = false;
         // groups of rays along one axis (most packets are one group)
         uint64_t todo = wave_ballot(S.live);
         while (todo && !redo) {
@@ -1574,10 +1580,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                 const float dz = dz_of();
                 const float du = pick(B.ax, S.ray.dy, S.ray.dz, S.ray.dx), dv = pick(B.ax, S.ray.dz, S.ray.dx, S.ray.dy);
                 grp = wave_ballot(fabsf(du) <= 2.0f * dz && fabsf(dv) <= 2.0f * dz) & todo & wave_ballot(S.live);
-                if (!grp) {  // a direction without a largest component (not a number)
-                    redo = true;
-                    break;
-                }
+                if (!grp) break;  // a direction without a largest component (not a number)
                 const bool on = __builtin_amdgcn_inverse_ballot_w64(grp);
                 const float oz = B.sg * pick(B.ax, S.ray.ox, S.ray.oy, S.ray.oz);
                 B.z0 = wave_min(on ? oz : kInf);
@@ -1606,13 +1609,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
             }
             todo &= ~grp;
             // rays that share little: most leaves of the bundle would be tested for nothing
-            if (held > kFrontHeld) {
-                redo = true;
-                break;
-            }
+            if (held > kFrontHeld) continue;
+            leave = false;
             int rounds = 0;
             // rounds, until the group's rays have stopped or run out of hits
-            for (uint64_t on_mask = grp & wave_ballot(S.live); on_mask && !redo; on_mask = grp & wave_ballot(S.live)) {
+            for (uint64_t on_mask = grp & wave_ballot(S.live); on_mask && !leave && !redo; on_mask = grp & wave_ballot(S.live)) {
                 if (COUNT) ++cnt.round;
                 hb.clear();
                 double cap = F.stop[lane];
@@ -1663,7 +1664,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                 int windows = 0;
                 for (bool more = true; more;) {
                     if (++windows > kFrontWindows) {
-                        redo = true;
+                        leave = true;
                         break;
                     }
                     // ---- expand the window's nodes, and test the leaves found against the bundle
@@ -1691,7 +1692,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                             continue;
                         }
                         if (nA >= kFrontActive) {
-                            redo = true;
+                            leave = true;
                             break;
                         }
                         // children: at most 2 m more leaves and nodes
@@ -1735,7 +1736,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                         }
                         __syncthreads();
                     }
-                    if (redo) break;
+                    if (leave) break;
 
                     // ---- the window's leaves in depth order: a counting sort over 64 depth bins
                     F.hist[lane] = 0u;
@@ -1968,7 +1969,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                     }
                     nN = keep_n;
                 }
-                if (redo) break;
+                if (leave || redo) break;
                 // a lane that lost nothing has consumed all its hits, every other live one those in front of
                 // its cap
                 if (__builtin_amdgcn_inverse_ballot_w64(on_mask) && !(cap < F.stop[lane])) S.live = false;
@@ -1976,16 +1977,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                 const uint64_t left = grp & wave_ballot(S.live);
                 const float from = hit_key_t(cap);
                 const uint64_t ahead = wave_ballot(S.last > F.start[lane]) | wave_ballot(from > F.from[lane]);
-                redo = left != 0 && (((left & ahead) == 0 && left == began) || ++rounds > kFrontRounds);
+                leave = left != 0 && (((left & ahead) == 0 && left == began) || ++rounds > kFrontRounds);
                 if (__builtin_amdgcn_inverse_ballot_w64(grp)) F.from[lane] = fmaxf(F.from[lane], from);
                 rejoin();
             }
         }
         const LaneRay LR = lane_ray(P, ptr, pkt, lane);
         if (redo) {
-            // start over with the walk; the packet's first list chunk is used again
             lane_reset(S, cold, LR.valid && P.n_gauss > 0 && LR.tmax > P.t_min, lane);
-            LC = ListCursor{0, LC.first, 0, 0, LC.first, true};
+            LC = ListCursor{0, -1, 0, 0, LC.chunk, true};
+        }
+        if (wave_ballot(S.live)) {
             if (!walk_rounds<HitBuf<K>, false, false, COUNT, false>(S, cold, LR, zc, lists, LC, records, nodes, gidx, inv,
                                                                          ptr, P, hb, lane, cnt))
                 if (lane == 0) atomicOr(ptr.status, kStatusStack);

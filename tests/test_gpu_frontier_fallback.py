@@ -1,0 +1,53 @@
+"""What the frontier forward leaves to the walk: rays whose bundle is too wide
+go on in the same packet, with the same hits and no more of the list pool."""
+
+import numpy as np
+import pytest
+
+from synthetic import scenes
+from synthetic.cameras import look_at_camera, pinhole_rays
+
+pytestmark = pytest.mark.gpu
+
+
+def _g():
+    import tests._gpu as G
+    from paper_2501_19196_amd import renderer as R
+    return G, R
+
+
+def _same_lists(R, rays, pa, sa, pb, sb, cap):
+    la, lb = R.hit_lists(rays, pa, sa, cap=cap), R.hit_lists(rays, pb, sb, cap=cap)
+    np.testing.assert_array_equal(la["count"], lb["count"])
+    np.testing.assert_array_equal(lb["stored"], lb["count"])
+    np.testing.assert_array_equal(la["stored"], la["count"])
+    np.testing.assert_array_equal(la["ids"], lb["ids"])
+
+
+def test_a_group_left_to_the_walk_takes_no_second_pool():
+    """Every packet holds eight rays of a camera and eight that span the scene along another axis: the second
+    group is left to the walk after the first has stored its rows, and the pool is sized for one set of rows."""
+    print("case two groups, lists", flush=True)
+    G, R = _g()
+    sc = scenes.scene_config4(seed=98, n=100000)
+    o1, d1 = pinhole_rays(look_at_camera((0, -7, 3.5), (0, 0, 0.5), (0, 0, 1), 64, 32, fov_y_deg=25))
+    rng = np.random.default_rng(98)
+    n = o1.shape[0]
+    o2 = np.float32(np.column_stack([np.full(n, -8.0), rng.uniform(-4, 4, n), rng.uniform(0, 3, n)]))
+    d2 = np.float32(np.column_stack([np.ones(n), rng.uniform(-0.3, 0.3, (n, 2))]))
+    o = np.concatenate([o1.reshape(-1, 8, 3), o2.reshape(-1, 8, 3)], axis=1).reshape(-1, 3)
+    d = np.concatenate([d1.reshape(-1, 8, 3), d2.reshape(-1, 8, 3)], axis=1).reshape(-1, 3)
+    pc = R.Params(hit_list=512, flags=8)
+    _, _, s, (bvh, g, rays) = G.render(sc, o, d, pc)
+    c = R.read_counters(bvh)
+    per_ray = c["list_slots"] / (2 * n)
+    print(c, "slots a ray", per_ray, flush=True)
+    assert s == 0 and c["packets"] == 2 * n // 16
+    # room for the rows, the last chunk of each packet (8 slots a ray) and what its chunks leave over
+    p = R.Params(hit_list=int(np.ceil(1.15 * per_ray)) + 8)
+    out, st, s, _ = G.render(sc, o, d, p, bvh=bvh, g=g)
+    pw = R.Params(hit_list=512, stack_depth=64)
+    ref, st0, s0, _ = G.render(sc, o, d, pw, bvh=bvh, g=g)
+    assert s == 0 and s0 == 0
+    np.testing.assert_array_equal(out, ref)
+    _same_lists(R, rays, p, st, pw, st0, 512)
