@@ -1147,10 +1147,9 @@ __device__ inline void add_counts(const FwdCount &c, const Ptrs &ptr, int lane)
     atomicAdd(ptr.counters + 14, (unsigned long long)c.slots);
 }
 
-// The depth-first walk of a packet, in rounds, until no lane is live. OCTS: specialised on the
-// direction octant (else one generic form, where the walk is the exception). Returns false when
-// the traversal stack overflowed.
-template <typename BUF, bool BRUTE, bool OCTS, bool COUNT, bool PAPER>
+// The depth-first walk of a packet, in rounds, until no lane is live. Returns false when the traversal
+// stack overflowed.
+template <typename BUF, bool BRUTE, bool COUNT, bool PAPER>
 __device__ inline bool walk_rounds(LaneState &S, LaneCold &C, const LaneRay &LR, bool zc, bool lists, ListCursor &LC,
                                    const float4 *__restrict__ records, const float4 *__restrict__ nodes,
                                    const int32_t *__restrict__ gidx, const int32_t *__restrict__ inv, const Ptrs &ptr,
@@ -1161,7 +1160,7 @@ __device__ inline bool walk_rounds(LaneState &S, LaneCold &C, const LaneRay &LR,
     const float tmax = LR.tmax;
     bool &live = S.live;
     const Slab sl = make_slab(ray);
-    const int oct = OCTS ? wave_octant(sl, LR.valid) : kMixedOctant;
+    const int oct = wave_octant(sl, LR.valid);
     bool overflow = false;
     uint64_t c_node = 0, c_lchild = 0;
     while (wave_ballot(live)) {
@@ -1209,12 +1208,10 @@ __device__ inline bool walk_rounds(LaneState &S, LaneCold &C, const LaneRay &LR,
 
         if (BRUTE) {
             for (int64_t j = 0; j < P.n_gauss; ++j) leaf(j);
-        } else if (OCTS) {
+        } else {
             // While-while traversal: descend internal nodes until a leaf is reached (or the
             // stack runs dry), then test that leaf; the hit buffer changes only in the leaf step.
             RS_WALK_BVH()
-        } else {
-            RS_WALK_OCT(kMixedOctant)
         }
         if (overflow) {
             live = false;
@@ -1282,8 +1279,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(waves_for(K,
             hb.ring = ring;
             hb.lane = lane;
         }
-        if (!walk_rounds<typename FwdBuf<K>::type, BRUTE, true, COUNT, true>(S, cold, LR, zc, lists, LC, records, nodes,
-                                                                             gidx, inv, ptr, P, hb, lane, cnt))
+        if (!walk_rounds<typename FwdBuf<K>::type, BRUTE, COUNT, true>(S, cold, LR, zc, lists, LC, records, nodes, gidx, inv, ptr,
+                                                                       P, hb, lane, cnt))
             if (lane == 0) atomicOr(ptr.status, kStatusStack);
         write_rays(S, cold, LR, R, ptr, LC, lists, lane);
         if (COUNT) {
@@ -1323,11 +1320,23 @@ constexpr int kFrontSorted = 192;  // leaves tested ray by ray per window at mos
 constexpr int kFrontRaw = 128;     // leaves found, not yet tested
 constexpr int kFrontWindows = 1 << 14, kFrontRounds = 4096;  // windows of a round, rounds of a packet: then the walk
 constexpr float kFrontFirst = 1.0f;     // Gaussians held that the first window is made for (0.5: 5.7, 1.5: 5.3 ms at 1M; 1.5, 1.8 at 100k)
-// Gaussians a bundle may hold, by volume; beyond that the packet is walked. Rays off curved mirrors span
-// most of the scene, and a bundle drops little of it. (500k Gaussians, 4 x 1024x768 with mirrors: 22 ms at
-// 512 to 2048, 144 at 4096, 34 when all is walked; 1M, 320x180 with lists: 9.6, 6.2 and 5.2 ms at 512, 2048
-// and 4096.)
-constexpr float kFrontHeld = 2048.0f;
+// Gaussians a bundle may hold, by volume; beyond that the packet is walked, since a bundle that spans much of the
+// scene drops little of it. (500k Gaussians, 4 x 1024x768 with mirrors: 22 ms at 512 to 2048, 144 at 4096, 34 when all
+// is walked; 1M, 320x180 with lists: 9.6, 6.2 and 5.2 ms at 512, 2048 and 4096.) A walk costs less the smaller the
+// scene, so the bound is a share of it too. (30k, 320x240 with a mirror and shadows: 1.4 ms walked from 469 on, 15.8
+// from 2048 on.)
+constexpr float kFrontHeld = 2048.0f, kFrontHeldLeast = 256.0f, kFrontShare = 1.0f / 64.0f;
+// A frontier also gives way to the walk while it is at work, which the volume alone does not foresee:
+// - where most leaves that it tests ray by ray are hit by none: after kFrontTested pairs, when under a quarter had a hit
+//   (the case above, were it not for its volume: 98 % without a hit, 50000 leaves);
+// - where many rays need many rounds, each of them searched from the root: the walk shares its visits among the
+//   rays that are left, a frontier of few rays is narrow. Rounds, and rays left, of 64-ray packets and of smaller ones:
+//   10k large translucent Gaussians, 640x480: 10.3 ms (11.5 in the frontier, 10.9 walked); 3k: 7.0 (10.0, 7.6);
+//   500k, 640x361 with mirrors: 10.6 (19.5, 10.5); 1M, 1920x1080: 4.8 (5.3, 7.8). With 24 rays left after three rounds
+//   100k, 800x800 takes 1.9 ms (1.6); 16-ray packets after four rounds with eight left: 1M, 320x180 with lists 6.8
+//   (5.8 here), 500k, 160x120 with mirrors 11 (16 here, 17 walked, 30 in the frontier).
+constexpr int kFrontTested = 256;
+constexpr int kWideRounds = 4, kWideLeft = 24, kSmallRounds = 8, kSmallLeft = 14;
 constexpr float kFrontBack = 4e-3f;       // of the depth from which a later round tests boxes, relative
 constexpr float kFrontMargin = 1.2e-4f;  // of a depth bound, relative: the rounding of t1 of flat ellipsoids
 
@@ -1527,6 +1536,15 @@ constexpr int64_t kFrontFew = 2048;
 constexpr int kFrontDrain = 32;  // lanes with a final hit that make a drain step worth while
 constexpr int kFrontDefault = 24;
 
+// kNoHit made where it is used: as a constant of the whole kernel it is spilled, and each insertion waits
+// for it (5 % of the frontier's time).
+__device__ inline double no_hit_here()
+{
+    uint32_t lo, hi;
+    asm volatile("v_mov_b32 %0, 0\n\tv_mov_b32 %1, 0x7ff00000" : "=&v"(lo), "=v"(hi));
+    return __longlong_as_double((long long)((uint64_t(hi) << 32) | lo));
+}
+
 template <int K, bool COUNT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_render_front(
     const float4 *__restrict__ records, const float4 *__restrict__ nodes, const int32_t *__restrict__ gidx,
@@ -1609,9 +1627,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
             }
             todo &= ~grp;
             // rays that share little: most leaves of the bundle would be tested for nothing
-            if (held > kFrontHeld) continue;
+            if (held > fminf(kFrontHeld, fmaxf(kFrontHeldLeast, kFrontShare * float(P.n_gauss)))) continue;
             leave = false;
-            int rounds = 0;
+            int rounds = 0, tested = 0, useful = 0;  // pairs of leaves tested ray by ray, and those that a ray hits
             // rounds, until the group's rays have stopped or run out of hits
             for (uint64_t on_mask = grp & wave_ballot(S.live); on_mask && !leave && !redo; on_mask = grp & wave_ballot(S.live)) {
                 if (COUNT) ++cnt.round;
@@ -1845,6 +1863,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                             }
                             front = __builtin_amdgcn_readlane(szv, ia);
                             if (front > reach) continue;
+                            ++tested;
                             const int64_t ja = __builtin_amdgcn_readlane(srv, ia), jb = __builtin_amdgcn_readlane(srv, ia + 1);
                             const float4 a0 = records[4 * ja], a1 = records[4 * ja + 1], a2 = records[4 * ja + 2],
                                          a3 = records[4 * ja + 3];
@@ -1862,6 +1881,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                             ma = wave_ballot(h2a <= P.Q) & on_mask;
                             mb = wave_ballot(h2b <= P.Q) & (i + 1 < nS ? on_mask : 0ull);
                             if ((ma | mb) == 0) continue;
+                            ++useful;
                             ta = ellipsoid_t1(ha, a2, h2a, P.Q);
                             tb = ellipsoid_t1(hb2, b2, h2b, P.Q);
                             ka = hit_key(ta, ga);
@@ -1915,8 +1935,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                         }
                         if (COUNT) cnt.lbuf += __popcll(ma) + __popcll(mb);
                         const bool ca = __builtin_amdgcn_inverse_ballot_w64(ma), cb = __builtin_amdgcn_inverse_ballot_w64(mb);
-                        if (ma) cap = min_bare(cap, hb.insert_out(ca ? ka : kNoHit));
-                        if (mb) cap = min_bare(cap, hb.insert_out(cb ? kb : kNoHit));
+                        if (ma) cap = min_bare(cap, hb.insert_out(ca ? ka : no_hit_here()));
+                        if (mb) cap = min_bare(cap, hb.insert_out(cb ? kb : no_hit_here()));
                         // once the hits found so far bring T below eps1 whatever their order, none behind the
                         // farthest of them is wanted
                         Tv *= (ca ? oma : 1.0f) * (cb ? omb : 1.0f);
@@ -1932,6 +1952,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                         }
                     }
                     if (redo || !on_mask) break;
+                    if (tested > kFrontTested && 4 * useful < tested) {
+                        leave = true;
+                        break;
+                    }
                     if (forced || !more) continue;
 
                     // ---- the next window starts at the nearest thing left
@@ -1977,7 +2001,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                 const uint64_t left = grp & wave_ballot(S.live);
                 const float from = hit_key_t(cap);
                 const uint64_t ahead = wave_ballot(S.last > F.start[lane]) | wave_ballot(from > F.from[lane]);
-                leave = left != 0 && (((left & ahead) == 0 && left == began) || ++rounds > kFrontRounds);
+                const bool wide = P.pkt_shift == 6;
+                leave = left != 0 && (((left & ahead) == 0 && left == began) || ++rounds > kFrontRounds ||
+                                      (rounds >= (wide ? kWideRounds : kSmallRounds) &&
+                                       __popcll(left) >= (wide ? kWideLeft : kSmallLeft)));
                 if (__builtin_amdgcn_inverse_ballot_w64(grp)) F.from[lane] = fmaxf(F.from[lane], from);
                 rejoin();
             }
@@ -1988,9 +2015,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
             LC = ListCursor{0, -1, 0, 0, LC.chunk, true};
         }
         if (wave_ballot(S.live)) {
-            if (!walk_rounds<HitBuf<K>, false, false, COUNT, false>(S, cold, LR, zc, lists, LC, records, nodes, gidx, inv,
-                                                                         ptr, P, hb, lane, cnt))
+            // with the stand-alone walk's buffer, its tail in the frontier's LDS
+            static_assert(sizeof(FrontLds) >= sizeof(double) * kTailKeys * kWave, "room for the tail");
+            using Buf = FwdBuf<48>::type;
+            Buf wb;
+            wb.ring = reinterpret_cast<double *>(&F);
+            wb.lane = lane;
+            __syncthreads();
+            if (!walk_rounds<Buf, false, COUNT, false>(S, cold, LR, zc, lists, LC, records, nodes, gidx, inv, ptr, P, wb, lane,
+                                                       cnt))
                 if (lane == 0) atomicOr(ptr.status, kStatusStack);
+            __syncthreads();
         }
         write_rays(S, cold, LR, ptr.set[LR.si], ptr, LC, lists, lane);
         if (COUNT) {

@@ -51,3 +51,61 @@ def test_a_group_left_to_the_walk_takes_no_second_pool():
     assert s == 0 and s0 == 0
     np.testing.assert_array_equal(out, ref)
     _same_lists(R, rays, p, st, pw, st0, 512)
+
+
+def _counts(R, G, sc, o, d, views, **kw):
+    p = R.Params(**{**kw, "flags": 8})
+    _, _, s, (bvh, _, _) = G.render(sc, o, d, p, views=views)
+    assert s == 0
+    return R.read_counters(bvh)
+
+
+def test_wide_bundles_are_walked_early():
+    """Parallel rays scattered over three units, sixteen a packet: the bundle holds a twentieth of the scene and
+    few of its leaves meet a ray. The packets test about as many leaves as a walk does."""
+    print("case wide bundles", flush=True)
+    G, R = _g()
+    sc = scenes.scene_config4(seed=98, n=30000)
+    rng = np.random.default_rng(3)
+    n = 1024
+    c = np.repeat(rng.uniform(-2, 2, (n // 16, 2)), 16, 0)
+    o = np.float32(np.column_stack([c + rng.uniform(-1.5, 1.5, (n, 2)), np.full(n, 6.0)]))
+    d = np.float32(np.column_stack([rng.uniform(-0.02, 0.02, (n, 2)), -np.ones(n)]))
+    a = _counts(R, G, sc, o, d, None, hit_list=128)
+    b = _counts(R, G, sc, o, d, None, hit_list=128, stack_depth=64)
+    print(a, b, flush=True)
+    assert a["packets"] == b["packets"] == n // 16
+    assert a["leaf_visits"] <= 2 * b["leaf_visits"]
+    p, pw = R.Params(hit_list=128), R.Params(hit_list=128, stack_depth=64)
+    out, st, s, (bvh, g, rays) = G.render(sc, o, d, p)
+    ref, st0, s0, _ = G.render(sc, o, d, pw, bvh=bvh, g=g)
+    assert s == 0 and s0 == 0
+    np.testing.assert_array_equal(out, ref)
+    _same_lists(R, rays, p, st, pw, st0, 128)
+
+
+@pytest.mark.parametrize("w,h,wide", [(64, 64, False), (320, 320, True)])
+def test_rays_of_many_rounds_go_on_in_the_walk(w, h, wide):
+    """Large translucent Gaussians, 512 hits a ray: after the frontier's rounds (4 of a 64-ray packet, 8 of a
+    16-ray one) the rays are walked from where they are, so there are that many rounds more than in a walk."""
+    print("case many rounds", w, h, flush=True)
+    G, R = _g()
+    sc = scenes.random_scene(93, 3000, box=0.6, scale_lo=0.1, scale_hi=0.3)
+    sc.opacity[:] = np.float32(0.02)
+    o, d = pinhole_rays(look_at_camera((0, 0, -3), (0, 0, 0), (0, 1, 0), w, h, fov_y_deg=20))
+    views = [(0, w, h)]
+    a, b = _counts(R, G, sc, o, d, views), _counts(R, G, sc, o, d, views, stack_depth=64)
+    print(a, b, flush=True)
+    assert a["packets"] == b["packets"] == o.shape[0] // (64 if wide else 16)
+    assert a["rounds"] > a["packets"] * (4 if wide else 8)  # the frontier's, then the walk's
+    assert a["rounds"] <= b["rounds"] + a["packets"] * (4 if wide else 8)
+    p, pw = R.Params(hit_list=768), R.Params(hit_list=768, stack_depth=64)
+    out, st, s, (bvh, g, rays) = G.render(sc, o, d, p, views=views)
+    ref, st0, s0, _ = G.render(sc, o, d, pw, views=views, bvh=bvh, g=g)
+    assert s == 0 and s0 == 0
+    np.testing.assert_array_equal(out, ref)
+    sel = np.arange(0, o.shape[0], 97)
+    la, lb = R.hit_lists(rays, p, st, cap=512, select=sel), R.hit_lists(rays, pw, st0, cap=512, select=sel)
+    assert (lb["count"] == 512).mean() > 0.5
+    for k in ("count", "stored", "ids"):
+        np.testing.assert_array_equal(la[k], lb[k])
