@@ -1334,9 +1334,10 @@ constexpr float kFrontHeld = 2048.0f, kFrontHeldLeast = 256.0f, kFrontShare = 1.
 //   10k large translucent Gaussians, 640x480: 10.3 ms (11.5 in the frontier, 10.9 walked); 3k: 7.0 (10.0, 7.6);
 //   500k, 640x361 with mirrors: 10.6 (19.5, 10.5); 1M, 1920x1080: 4.8 (5.3, 7.8). With 24 rays left after three rounds
 //   100k, 800x800 takes 1.9 ms (1.6); 16-ray packets after four rounds with eight left: 1M, 320x180 with lists 6.8
-//   (5.8 here), 500k, 160x120 with mirrors 11 (16 here, 17 walked, 30 in the frontier).
+//   (5.8 here). Launches of several sets give way sooner: reflected and shadow rays spread (500k, 160x120 with a
+//   mirror and shadows, lists: 9.4 ms; 15.7 after eight rounds, 16.6 walked, 30 in the frontier).
 constexpr int kFrontTested = 256;
-constexpr int kWideRounds = 4, kWideLeft = 24, kSmallRounds = 8, kSmallLeft = 14;
+constexpr int kWideRounds = 4, kWideLeft = 24, kSmallRounds = 8, kSmallLeft = 14, kSetsRounds = 2, kSetsLeft = 4;
 constexpr float kFrontBack = 4e-3f;       // of the depth from which a later round tests boxes, relative
 constexpr float kFrontMargin = 1.2e-4f;  // of a depth bound, relative: the rounding of t1 of flat ellipsoids
 
@@ -2001,10 +2002,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                 const uint64_t left = grp & wave_ballot(S.live);
                 const float from = hit_key_t(cap);
                 const uint64_t ahead = wave_ballot(S.last > F.start[lane]) | wave_ballot(from > F.from[lane]);
-                const bool wide = P.pkt_shift == 6;
+                const bool wide = P.pkt_shift == 6, sets = P.n_packets > P.packets_per_set;
                 leave = left != 0 && (((left & ahead) == 0 && left == began) || ++rounds > kFrontRounds ||
-                                      (rounds >= (wide ? kWideRounds : kSmallRounds) &&
-                                       __popcll(left) >= (wide ? kWideLeft : kSmallLeft)));
+                                      (rounds >= (wide ? kWideRounds : sets ? kSetsRounds : kSmallRounds) &&
+                                       __popcll(left) >= (wide ? kWideLeft : sets ? kSetsLeft : kSmallLeft)));
                 if (__builtin_amdgcn_inverse_ballot_w64(grp)) F.from[lane] = fmaxf(F.from[lane], from);
                 rejoin();
             }

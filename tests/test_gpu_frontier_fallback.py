@@ -1,5 +1,6 @@
-"""What the frontier forward leaves to the walk: rays whose bundle is too wide
-go on in the same packet, with the same hits and no more of the list pool."""
+"""What the frontier forward leaves to the walk: bundles that are too wide, leaves
+tested in vain, rays of many rounds. They go on in the same packet, with the same
+hits and no more of the list pool, and cost about what a walk does."""
 
 import numpy as np
 import pytest
@@ -109,3 +110,37 @@ def test_rays_of_many_rounds_go_on_in_the_walk(w, h, wide):
     assert (lb["count"] == 512).mean() > 0.5
     for k in ("count", "stored", "ids"):
         np.testing.assert_array_equal(la[k], lb[k])
+
+
+def test_secondary_sets_give_way_after_two_rounds():
+    """A mirror floor and shadows seen in 96x96 pixels: the packets of reflected and shadow rays spread, and test
+    about as many leaves in about as many rounds as a walk does, with its result."""
+    print("case secondary sets", flush=True)
+    G, R = _g()
+    import torch
+    sc = scenes.scene_config4(seed=98, n=500000)
+    cam = look_at_camera((4.2, 4.2, 3), (0, 0, 0.5), (0, 0, 1), 96, 96)
+    o, d = pinhole_rays(cam)
+    quad = np.float32([[-3, -3, 0], [3, -3, 0], [3, 3, 0], [-3, 3, 0]])
+    mesh = R.Mesh(G.dev(quad), G.dev(np.int32([[0, 1, 2], [0, 2, 3]])), G.dev(np.int32([1, 1])))
+    mbvh, sh, g, rays = R.build_mesh_bvh(mesh), R.Shading(), G.gaussians(sc), G.rays_of(o, d, [(0, 96, 96)])
+    got = []
+    for depth in (0, 64):
+        p = R.Params(hit_list=128, flags=8, stack_depth=depth)
+        bvh = R.build_bvh(g, p)
+        out, frame = R.render_mesh_fwd(bvh, mbvh, g, mesh, sh, rays, p)
+        torch.cuda.synchronize()
+        assert R.read_status(bvh) == 0
+        lists = [R.mesh_hit_lists(rays, p, sh, frame, k, cap=512) for k in range(3)]
+        got.append((out.cpu().numpy(), lists, R.read_counters(bvh)))
+    (img, lists, c), (ref, ref_lists, cw) = got
+    print(c, cw, flush=True)
+    np.testing.assert_array_equal(img, ref)
+    for a, b in zip(lists, ref_lists):
+        np.testing.assert_array_equal(a["count"], b["count"])
+        full = (a["stored"] == a["count"]) & (b["stored"] == b["count"])
+        assert full.mean() > 0.9
+        np.testing.assert_array_equal(a["ids"][full], b["ids"][full])
+    assert c["packets"] == cw["packets"] == 3 * 24 * 24
+    assert c["rounds"] <= cw["rounds"] + c["packets"]
+    assert c["leaf_visits"] <= 1.25 * cw["leaf_visits"]
