@@ -31,11 +31,12 @@ inline int tile_shift_of(const rs_params *p)
 // Forward and adjoint, 16-ray against 64-ray packets: 3000 Gaussians, 77k rays 0.30 and 0.33 ms, 128k rays
 // 0.40 and 0.33; 300k, 480x320 2.6 and 4.1; 500k, 640x480 4.9 and 4.2; 1M, 480x320 7.4 and 13.6, 640x480 8.1
 // and 8.1; 260k, three views of 406x228 and four of 203x85 6.3 and 12.9. The paper variant keeps 64: its
-// pool bound counts on 64-ray rows.
+// pool bound counts on 64-ray rows. So does brute force, whose packets each test every Gaussian (20k, 98304 rays:
+// 12.9 ms, 22.2 in 16-ray packets).
 constexpr int64_t kSmallLaunchRays = 98304, kMidLaunchRays = 524288, kSmallViewRays = 196608;
 inline int packet_shift(const rs_rays *rays, int64_t sets, const rs_params *p, int64_t n_gauss)
 {
-    if (p && (p->flags & RS_PAPER_GRADIENT)) return 6;
+    if (p && (p->flags & (RS_PAPER_GRADIENT | RS_BRUTE_FORCE))) return 6;
     const int64_t n = rays->n * sets, per_view = rays->n / (rays->n_views > 0 ? rays->n_views : 1);
     const bool small_views = n <= kMidLaunchRays && per_view <= kSmallViewRays && n_gauss >= per_view;
     return n <= kSmallLaunchRays || small_views ? 4 : 6;
