@@ -1308,10 +1308,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(waves_for(K,
 // A node is dropped when its box misses the bundle; a leaf when its ellipsoid does (its support
 // against the four planes) or when it misses the tube around the bundle's centre line.
 //
-// Correctness does not rest on the order: lower bounds carry a margin, a lane whose buffer
-// overflows remembers the smallest key it lost (`cap`), takes no hit beyond it and is traced
-// again from its last consumed key, and a hit found after a later one was consumed makes the
-// packet start over with the walk. So the result is the walk's bit for bit.
+// The result is the walk's bit for bit as long as no bound is too tight: a leaf that the bundle drops is not
+// tested, and a lane that has stopped looks for no nearer hit. So the bounds carry margins for the
+// rounding of the ray test (kFrontMargin of a depth, Bundle::pad of a length: camera and scene at 1, 50 and 1000 units
+// from the coordinate origin, one ray to sixteen, along an axis or not, some 50 million hits, four fifths of them on
+// flat Gaussians near their rim: none dropped, none in front of its bound). The rest does not hang on them:
+// a lane whose buffer overflows remembers the smallest key it lost (`cap`), takes no hit beyond it and is traced
+// again from its last consumed key, and a hit found after a later one was consumed makes the packet start over
+// with the walk.
 
 constexpr int kFrontActive = 256;  // nodes to expand in this window
 constexpr int kFrontNodes = 192;   // nodes beyond this window
@@ -1389,7 +1393,7 @@ struct Bundle {
     float Au0, Au1, Mu0, Mu1, Av0, Av1, Mv0, Mv1;
     float ru0, ru1, rv0, rv1;  // 1 / M
     float zfrom, zlo, zhi;  // hits are wanted from zfrom (zlo for boxes) to zhi
-    float pad;       // absolute slack: rounding at the scale of the origins
+    float pad;       // absolute slack: rounding at the scale of the origins and of the scene
 };
 
 __device__ inline float pick(int ax, float x, float y, float z) { return ax == 0 ? x : (ax == 1 ? y : z); }
@@ -1603,13 +1607,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                 const bool on = __builtin_amdgcn_inverse_ballot_w64(grp);
                 const float oz = B.sg * pick(B.ax, S.ray.ox, S.ray.oy, S.ray.oz);
                 B.z0 = wave_min(on ? oz : kInf);
-                B.pad = 2e-6f * wave_max(on ? fabsf(S.ray.ox) + fabsf(S.ray.oy) + fabsf(S.ray.oz) : 0.0f);
+                B.pad = wave_max(on ? fabsf(S.ray.ox) + fabsf(S.ray.oy) + fabsf(S.ray.oz) : 0.0f);
             }
+            // The ray test rounds in proportion to the offset between origin and mean, some 4e-7 of it
+            auto reach_of = [](float x, float y) { return fmaxf(fabsf(x), fabsf(y)); };
             float held = 0.0f;  // Gaussians in the bundle, by volume
             if (P.root >= 0) {
                 const float4 n0 = nodes[0], n1 = nodes[1], n2 = nodes[2];
                 const float lx = fminf(n0.x, n1.z), ly = fminf(n0.y, n1.w), lz = fminf(n0.z, n2.x);
                 const float hx = fmaxf(n0.w, n2.y), hy = fmaxf(n1.x, n2.z), hz = fmaxf(n1.y, n2.w);
+                B.pad = 2e-6f * fmaxf(B.pad, reach_of(lx, hx) + reach_of(ly, hy) + reach_of(lz, hz));
                 const float za = (B.sg > 0.0f ? pick(B.ax, lx, ly, lz) : -pick(B.ax, hx, hy, hz)) - B.z0;
                 const float zb = (B.sg > 0.0f ? pick(B.ax, hx, hy, hz) : -pick(B.ax, lx, ly, lz)) - B.z0;
                 const float eu = pick(B.ax, hy - ly, hz - lz, hx - lx), ev = pick(B.ax, hz - lz, hx - lx, hy - ly);
@@ -1625,8 +1632,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                     const float wu = fmaxf(span(au + z0 * mu), span(au + z1 * mu)), wv = fmaxf(span(av + z0 * mv), span(av + z1 * mv));
                     held = fminf(wu, eu) * fminf(wv, ev) * (z1 - z0) * float(P.n_gauss) / (eu * ev * (zb - za));
                 }
+            } else {
+                const float4 r3 = records[3];
+                B.pad = 2e-6f * fmaxf(B.pad, fabsf(r3.x) + fabsf(r3.y) + fabsf(r3.z));
             }
             todo &= ~grp;
+            if (!(B.pad < 1e30f)) continue;  // an origin that is not finite: no bound holds for the others
             // rays that share little: most leaves of the bundle would be tested for nothing
             if (held > fminf(kFrontHeld, fmaxf(kFrontHeldLeast, kFrontShare * float(P.n_gauss)))) continue;
             leave = false;
