@@ -1540,6 +1540,7 @@ __device__ inline double min_bare(double a, double b)
 constexpr int64_t kFrontFew = 2048;
 constexpr int kFrontDrain = 32;  // lanes with a final hit that make a drain step worth while
 constexpr int kFrontDefault = 24;
+constexpr int kFrontWaves = 4;  // per SIMD
 
 // kNoHit made where it is used: as a constant of the whole kernel it is spilled, and each insertion waits
 // for it (5 % of the frontier's time).
@@ -1551,7 +1552,7 @@ __device__ inline double no_hit_here()
 }
 
 template <int K, bool COUNT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_render_front(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFrontWaves))) void k_render_front(
     const float4 *__restrict__ records, const float4 *__restrict__ nodes, const int32_t *__restrict__ gidx,
     const int32_t *__restrict__ inv, const Ptrs ptr, const RenderParams P)
 {
@@ -2526,12 +2527,21 @@ int launch_sets(const BvhDesc &D, const rs_gaussians *g, const rs_params *p, int
     if (pass == Pass::Forward && P.lists) reset_pool(pool, pkt_shift, st);
     if (P.n_packets > 0) {
         KernArgs a;
+        const int kbuf = p->kbuf > 0 ? p->kbuf : P.front ? kFrontDefault : 48;
         if (P.persistent) {
             k_zero_queue<<<1, 64, 0, st>>>(h->xq);
             int dev = 0, cus = 256;
             (void)hipGetDevice(&dev);
             (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-            const int64_t waves = int64_t(cus) * 24;  // up to 6 waves per SIMD (the most any variant fits)
+            // A workgroup for each wave that the CUs hold of this kernel; those beyond start late and find empty queues
+            // (30k Gaussians, 400x300 with a mirror and shadows, forward: 1.25 ms; 1.35 at six waves per SIMD). The
+            // list adjoint, which could hold seven, takes six: its waves' line atomics get in each other's way (500k,
+            // 280x210 with a mirror 1.12 ms, 1.21 at seven; 4 x 1024x768 9.19 and 8.98). Brute force at 8 keys fits
+            // one more than its target.
+            const int per_simd = pass == Pass::AdjointList ? 6
+                                 : P.front                 ? kFrontWaves
+                                                           : waves_for(kbuf, pass != Pass::Forward) + P.brute;
+            const int64_t waves = int64_t(cus) * 4 * per_simd;
             a.grid = int(waves < P.n_packets ? waves : P.n_packets);
         } else {
             a.grid = plain_grid(P.n_packets);
@@ -2549,16 +2559,14 @@ int launch_sets(const BvhDesc &D, const rs_gaussians *g, const rs_params *p, int
                 k_adjoint_list<false><<<a.grid, kWave, 0, st>>>(a.records, a.inv, ptr, P);
         } else if (P.front) {
             // three buffer sizes: kbuf names the nearest
-            const int K = p->kbuf > 0 ? p->kbuf : kFrontDefault;
-            if (K <= 16)
+            if (kbuf <= 16)
                 launch_front<16>(a, ptr, P, st);
-            else if (K <= 24)
+            else if (kbuf <= 24)
                 launch_front<24>(a, ptr, P, st);
             else
                 launch_front<32>(a, ptr, P, st);
         } else {
-            const int K = p->kbuf > 0 ? p->kbuf : 48;
-            switch (K) {
+            switch (kbuf) {
             case 8: launch_k<8>(pass, a, ptr, P, st); break;
             case 16: launch_k<16>(pass, a, ptr, P, st); break;
             case 24: launch_k<24>(pass, a, ptr, P, st); break;
