@@ -250,7 +250,8 @@ typedef struct {
 /* Times every candidate on the caller's own BVH, Gaussians and rays: kbuf in
  * {8, 16, 24, 32, 48} x {one workgroup per packet, persistent queue} x tile width
  * {8, 16} (8x8 / 16x4 pixels; only 8 when the rays carry no views). Each runs
- * once untimed, then `reps` (1..100) times between hipEvents on `stream`.
+ * once untimed, then `reps` (1..100) times between hipEvents on `stream`; one that
+ * launches the same kernel on the same packets as an earlier one takes its time.
  * grad_rgb (device [n][3], optional) also times the adjoint, which then
  * needs ray_state and grads; out_rgb, ray_state and grads receive the
  * results of the last candidate run. Host-synchronous (waits for `stream`).

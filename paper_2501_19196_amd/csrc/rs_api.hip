@@ -344,6 +344,20 @@ int rs_autotune(const rs_bvh *bvh, const rs_gaussians *g, const rs_rays *rays, c
     static const int kbufs[5] = {8, 16, 24, 32, 48};
     const int n_tiles = rays->n_views > 0 ? 2 : 1;
     int best_f = -1, best_b = -1;
+    // Candidates that launch the same kernel on the same packets share a time: the frontier has three buffers for the
+    // five sizes, and launches of small packets leave the tile width aside.
+    const bool front = front_route(rays, 1, base, D.n, ray_state && base->hit_list > 0 && rays->n > 0);
+    const bool tiled = packet_shift(rays, 1, base, D.n) == 6;
+    const auto twin = [&](int c, bool fwd) {
+        for (int k = 0; k < c; ++k) {
+            const bool keys = fwd && front ? front_keys(result->kbuf[k]) == front_keys(result->kbuf[c])
+                                           : result->kbuf[k] == result->kbuf[c];
+            if (keys && result->persistent[k] == result->persistent[c] &&
+                (!tiled || result->tile_width[k] == result->tile_width[c]))
+                return k;
+        }
+        return -1;
+    };
     for (int ki = 0; ki < 5 && !e; ++ki) {
         for (int pers = 0; pers < 2 && !e; ++pers) {
             for (int ti = 0; ti < n_tiles && !e; ++ti) {
@@ -355,11 +369,20 @@ int rs_autotune(const rs_bvh *bvh, const rs_gaussians *g, const rs_rays *rays, c
                 result->kbuf[c] = p.kbuf;
                 result->persistent[c] = pers;
                 result->tile_width[c] = p.tile_width;
-                e = timed([&] { return launch_render(D, g, rays, &p, out_rgb, ray_state, nullptr, nullptr, st); },
-                          result->ms_fwd[c]);
-                if (!e && grad_rgb)
-                    e = timed([&] { return launch_render(D, g, rays, &p, nullptr, ray_state, grad_rgb, grads, st); },
-                              result->ms_bwd[c]);
+                const int f = twin(c, true), b = grad_rgb ? twin(c, false) : -1;
+                auto forward = [&] { return launch_render(D, g, rays, &p, out_rgb, ray_state, nullptr, nullptr, st); };
+                if (f < 0)
+                    e = timed(forward, result->ms_fwd[c]);
+                else
+                    result->ms_fwd[c] = result->ms_fwd[f];
+                if (b >= 0) {
+                    result->ms_bwd[c] = result->ms_bwd[b];
+                } else if (!e && grad_rgb) {
+                    if (f >= 0) e = forward();  // the adjoint reads a state of its own packets
+                    if (!e)
+                        e = timed([&] { return launch_render(D, g, rays, &p, nullptr, ray_state, grad_rgb, grads, st); },
+                                  result->ms_bwd[c]);
+                }
                 if (e) break;
                 if (best_f < 0 || result->ms_fwd[c] < result->ms_fwd[best_f]) {
                     best_f = c;

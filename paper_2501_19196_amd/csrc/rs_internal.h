@@ -50,6 +50,19 @@ inline int packet_shift_no_lists(const rs_rays *rays, int64_t sets, const rs_par
     const int ps = packet_shift(rays, sets, p, n_gauss);
     return ps == 4 && n_gauss >= 4 * rays->n * sets ? 2 : ps;
 }
+// Scenes of up to this many Gaussians are walked where a launch has packets enough to fill the chip: a frontier
+// has fixed costs (1000 Gaussians, 588x587: 100 us walked, 115 in windows; 3000: 248 and 232).
+constexpr int64_t kFrontFew = 2048;
+// Whether a forward pass takes the frontier kernel. It keeps no stack: a call that bounds the stack takes the walk. So
+// does the paper variant (its pool bound, see k_render), and so do the sets of paths of several bounces: refracted
+// rays of a packet go all ways (150k Gaussians, 640x361, three bounces: 7.7 ms walked, 9.2 to 22 otherwise).
+inline bool front_route(const rs_rays *rays, int sets, const rs_params *p, int64_t n_gauss, bool lists)
+{
+    return !(p->flags & RS_BRUTE_FORCE) && !((p->flags & RS_PAPER_GRADIENT) && lists) && p->stack_depth == 0 && sets <= 3 &&
+           (n_gauss > kFrontFew || packet_shift(rays, sets, p, n_gauss) < 6);
+}
+// The hits that a frontier's buffer holds for a kbuf.
+inline int front_keys(int kbuf) { return kbuf == 0 ? 24 : kbuf <= 16 ? 16 : kbuf <= 24 ? 24 : 32; }
 constexpr int kSortBlock = 256;
 constexpr int kSortItems = 8;  // keys per thread per sort tile
 constexpr int kSortTile = kSortBlock * kSortItems;

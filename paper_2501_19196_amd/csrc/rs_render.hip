@@ -1535,11 +1535,7 @@ __device__ inline double min_bare(double a, double b)
     return r;
 }
 
-// Scenes of up to this many Gaussians are walked where a launch has packets enough to fill the chip: a frontier
-// has fixed costs (1000 Gaussians, 588x587: 100 us walked, 115 in windows; 3000: 248 and 232).
-constexpr int64_t kFrontFew = 2048;
 constexpr int kFrontDrain = 32;  // lanes with a final hit that make a drain step worth while
-constexpr int kFrontDefault = 24;
 constexpr int kFrontWaves = 4;  // per SIMD
 
 // kNoHit made where it is used: as a constant of the whole kernel it is spilled, and each insertion waits
@@ -2481,13 +2477,7 @@ int launch_sets(const BvhDesc &D, const rs_gaussians *g, const rs_params *p, int
     P.persistent = (p->flags & RS_PERSISTENT) ? 1 : 0;
     P.brute = (p->flags & RS_BRUTE_FORCE) ? 1 : 0;
     P.count = (p->flags & RS_COUNTERS) ? 1 : 0;
-    // the frontier kernel keeps no stack: a call that bounds the stack takes the walk. So does the paper variant (its
-    // pool bound, see k_render), and so do the sets of paths
-    // of several bounces: refracted rays of a packet go all ways (150k Gaussians, 640x361, three bounces: 7.7 ms
-    // walked, 9.2 to 22 otherwise).
-    const bool paper = (p->flags & RS_PAPER_GRADIENT) && room.units > 0;
-    P.front = pass == Pass::Forward && !P.brute && !paper && p->stack_depth == 0 && nsets <= 3 &&
-              (D.n > kFrontFew || packet_shift(rays, nsets, p, D.n) < 6);
+    P.front = pass == Pass::Forward && front_route(rays, nsets, p, D.n, room.units > 0);
     const int pkt_shift = P.front && room.units == 0 ? packet_shift_no_lists(rays, nsets, p, D.n)
                                                      : packet_shift(rays, nsets, p, D.n);
     const ListPool pool = list_pool_at(room, chunk_slots_of(pkt_shift));
@@ -2497,7 +2487,7 @@ int launch_sets(const BvhDesc &D, const rs_gaussians *g, const rs_params *p, int
     P.strip_tiles = kStripTiles;
     P.lists = pool.chunks > 0 ? 1 : 0;
     P.overflow_only = (pass == Pass::AdjointTraverse && P.lists) ? 1 : 0;
-    P.paper = paper ? 1 : 0;
+    P.paper = (p->flags & RS_PAPER_GRADIENT) && P.lists ? 1 : 0;
     P.eps2 = p->eps2;
     P.chunk = (P.n_packets + kXcdQueues - 1) / kXcdQueues;
 
@@ -2527,7 +2517,7 @@ int launch_sets(const BvhDesc &D, const rs_gaussians *g, const rs_params *p, int
     if (pass == Pass::Forward && P.lists) reset_pool(pool, pkt_shift, st);
     if (P.n_packets > 0) {
         KernArgs a;
-        const int kbuf = p->kbuf > 0 ? p->kbuf : P.front ? kFrontDefault : 48;
+        const int kbuf = P.front ? front_keys(p->kbuf) : p->kbuf > 0 ? p->kbuf : 48;
         if (P.persistent) {
             k_zero_queue<<<1, 64, 0, st>>>(h->xq);
             int dev = 0, cus = 256;
@@ -2558,13 +2548,11 @@ int launch_sets(const BvhDesc &D, const rs_gaussians *g, const rs_params *p, int
             else
                 k_adjoint_list<false><<<a.grid, kWave, 0, st>>>(a.records, a.inv, ptr, P);
         } else if (P.front) {
-            // three buffer sizes: kbuf names the nearest
-            if (kbuf <= 16)
-                launch_front<16>(a, ptr, P, st);
-            else if (kbuf <= 24)
-                launch_front<24>(a, ptr, P, st);
-            else
-                launch_front<32>(a, ptr, P, st);
+            switch (kbuf) {
+            case 16: launch_front<16>(a, ptr, P, st); break;
+            case 24: launch_front<24>(a, ptr, P, st); break;
+            default: launch_front<32>(a, ptr, P, st); break;
+            }
         } else {
             switch (kbuf) {
             case 8: launch_k<8>(pass, a, ptr, P, st); break;
