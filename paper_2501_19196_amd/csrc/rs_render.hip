@@ -1385,6 +1385,9 @@ __device__ inline uint32_t lanes_below(uint64_t m)
     return __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
 }
 
+// A wave-uniform value in a scalar register: vector registers are what the frontier is short of.
+__device__ inline float uniform(float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); }
+
 // A packet's axes and ray bundle (wave-uniform but for the lane's own ozr, dz).
 struct Bundle {
     int ax;      // axis of z; u and v are the next two
@@ -1393,6 +1396,7 @@ struct Bundle {
     float Au0, Au1, Mu0, Mu1, Av0, Av1, Mv0, Mv1;
     float ru0, ru1, rv0, rv1;  // 1 / M
     float zfrom, zlo, zhi;  // hits are wanted from zfrom (zlo for boxes) to zhi
+    float rq;        // sqrt(Q)
     float pad;       // absolute slack: rounding at the scale of the origins and of the scene
 };
 
@@ -1507,7 +1511,7 @@ __device__ inline bool ellipsoid_meets(const Bundle &B, float Q, const float4 r0
     const float ia = __builtin_amdgcn_rcpf(d0 * d0 + d1 * d1 + d2 * d2);
     const float b = D[0] * y[0] * d0 + D[1] * y[1] * d1 + D[2] * y[2] * d2;
     const float hh = (u0 * u0 + u1 * u1 + u2 * u2) * ia;
-    const float rr = __builtin_amdgcn_sqrtf(Q) + __builtin_amdgcn_sqrtf(g2 + 2.0f * fabsf(gd));
+    const float rr = B.rq + __builtin_amdgcn_sqrtf(g2 + 2.0f * fabsf(gd));
     const float disc = rr * rr * 1.001f - hh;
     out = out || disc < 0.0f;
     const float zc = -b * ia;
@@ -1517,7 +1521,7 @@ __device__ inline bool ellipsoid_meets(const Bundle &B, float Q, const float4 r0
     // A ray enters in front of its point nearest to the centre. With w the ray's (whitened) offset from
     // the line at zc and w1 its change per depth, that point lies (<q, w1> + <w, d' + w1>) / |d' + w1|^2
     // from zc, |q| <= rr, |w| <= delta, |w1| <= delta / zf; used where |w1| <= |d'| / 2
-    const float delta = rr - __builtin_amdgcn_sqrtf(Q), w1 = delta * __builtin_amdgcn_rcpf(zf);
+    const float delta = rr - B.rq, w1 = delta * __builtin_amdgcn_rcpf(zf);
     const float behind = 4.0f * rr * w1 * ia + 2.0f * delta * __builtin_amdgcn_sqrtf(ia);
     out = out || (w1 * w1 * ia <= 0.25f && zc + behind * 1.001f + slack < B.zfrom);
     // fmaxf returns the other operand for a NaN
@@ -1558,6 +1562,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFrontWaves)
     int64_t iter_pkt = 0;
     const int xcd = xcd_id();
     int qi = 0;
+    const float root_q = uniform(__builtin_amdgcn_sqrtf(P.Q)), closed_at = uniform(0.99f * P.eps1);
     FwdCount cnt{};
     for (;;) {
         const int64_t pkt = next_packet(P, ptr.queue, lane, xcd, qi, iter_pkt);
@@ -1590,6 +1595,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFrontWaves)
             auto of_leader = [&](float x) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), leader)); };
             const float lx = of_leader(S.ray.dx), ly = of_leader(S.ray.dy), lz = of_leader(S.ray.dz);
             Bundle B;
+            B.rq = root_q;
             B.ax = fabsf(lx) >= fabsf(ly) && fabsf(lx) >= fabsf(lz) ? 0 : (fabsf(ly) >= fabsf(lz) ? 1 : 2);
             B.sg = pick(B.ax, lx, ly, lz) >= 0.0f ? 1.0f : -1.0f;
             // the lane's direction and origin along z: z(t) = ozr + t dz
@@ -1613,7 +1619,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFrontWaves)
                 const float4 n0 = nodes[0], n1 = nodes[1], n2 = nodes[2];
                 const float lx = fminf(n0.x, n1.z), ly = fminf(n0.y, n1.w), lz = fminf(n0.z, n2.x);
                 const float hx = fmaxf(n0.w, n2.y), hy = fmaxf(n1.x, n2.z), hz = fmaxf(n1.y, n2.w);
-                B.pad = 2e-6f * fmaxf(B.pad, reach_of(lx, hx) + reach_of(ly, hy) + reach_of(lz, hz));
+                B.pad = uniform(2e-6f * fmaxf(B.pad, reach_of(lx, hx) + reach_of(ly, hy) + reach_of(lz, hz)));
                 const float za = (B.sg > 0.0f ? pick(B.ax, lx, ly, lz) : -pick(B.ax, hx, hy, hz)) - B.z0;
                 const float zb = (B.sg > 0.0f ? pick(B.ax, hx, hy, hz) : -pick(B.ax, lx, ly, lz)) - B.z0;
                 const float eu = pick(B.ax, hy - ly, hz - lz, hx - lx), ev = pick(B.ax, hz - lz, hx - lx, hy - ly);
@@ -1654,10 +1660,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFrontWaves)
                     const float dz = dz_of(), ozr = ozr_of();
                     const float tl = F.from[lane];
                     const float zl = wave_min(on ? __builtin_fmaf(tl, dz, ozr) : kInf);
-                    B.zfrom = fmaxf(zl - kFrontMargin * fabsf(zl) - B.pad, 0.0f);
-                    B.zlo = fmaxf(zl - kFrontBack * fabsf(zl) - B.pad, 0.0f);
+                    B.zfrom = uniform(fmaxf(zl - kFrontMargin * fabsf(zl) - B.pad, 0.0f));
+                    B.zlo = uniform(fmaxf(zl - kFrontBack * fabsf(zl) - B.pad, 0.0f));
                     const float zh = wave_max(on ? __builtin_fmaf(hit_key_t(cap), dz, ozr) : -kInf);
-                    B.zhi = zh + kFrontMargin * fabsf(zh) + B.pad;
+                    B.zhi = uniform(zh + kFrontMargin * fabsf(zh) + B.pad);
                     bundle_bounds(B, S.ray, on, ozr, dz);
                     n_on = __popcll(on_mask);
                 }
@@ -1841,7 +1847,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFrontWaves)
                     if (cut) {
                         const double c = bound_key(fmaxf((zcut - ozr_of()) * (1.0f / dz_of()), 0.0f));
                         cap = c < cap ? c : cap;
-                        B.zhi = fminf(B.zhi, zcut + kFrontMargin * zcut + B.pad);
+                        B.zhi = uniform(fminf(B.zhi, zcut + kFrontMargin * zcut + B.pad));
                     }
                     // everything in front of `done` has been found
                     float done = forced || partial ? S0 : (nbins == kWave ? S1 : S0 + float(nbins) * wbin);
@@ -1950,7 +1956,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFrontWaves)
                         // farthest of them is wanted
                         Tv *= (ca ? oma : 1.0f) * (cb ? omb : 1.0f);
                         tv = fmaxf(tv, fmaxf(ca ? ta : 0.0f, cb ? tb : 0.0f));
-                        const bool closed = Tv < 0.99f * P.eps1;
+                        const bool closed = Tv < closed_at;
                         if ((ma | mb) & wave_ballot(closed)) {
                             const double far = __longlong_as_double(__double_as_longlong(bound_key(tv)) + (1ll << 32));
                             cap = closed ? min_bare(cap, far) : cap;
@@ -1972,7 +1978,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFrontWaves)
                         const bool on = __builtin_amdgcn_inverse_ballot_w64(on_mask);
                         const float dz = dz_of(), ozr = ozr_of();
                         const float zh = wave_max(on ? __builtin_fmaf(hit_key_t(cap), dz, ozr) : -kInf);
-                        B.zhi = zh + kFrontMargin * fabsf(zh) + B.pad;
+                        B.zhi = uniform(zh + kFrontMargin * fabsf(zh) + B.pad);
                         if (2 * __popcll(on_mask) <= n_on) {  // half of the rays have stopped: a tighter bundle
                             bundle_bounds(B, S.ray, on, ozr, dz);
                             n_on = __popcll(on_mask);
