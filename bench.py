@@ -224,6 +224,13 @@ def main():
              torch.empty_like(g.opacity), torch.empty_like(g.rgb))
     ev = lambda: torch.cuda.Event(enable_timing=True)
 
+    def fwd_keys(p):
+        """Hits that a ray's buffer holds in the forward launched for p: the frontier has three sizes; the paper
+        variant and paths of several bounces are walked."""
+        if p.stack_depth or (p.flags & 16 and p.hit_list) or (shading is not None and shading.max_bounces > 1):
+            return p.kbuf or 48
+        return 24 if p.kbuf == 0 else 16 if p.kbuf <= 16 else 24 if p.kbuf <= 24 else 32
+
     def tune_for(p):
         """Autotuned (forward, adjoint) params for the stored-list setting of p."""
         bvh = R.build_bvh(g, p, workspace=ws)
@@ -445,7 +452,7 @@ def main():
         rec = json.load(open(os.path.join(ROOT, "profiles", "render_traffic.json")))
         src = b"".join(open(os.path.join(ROOT, "paper_2501_19196_amd", "csrc", f), "rb").read()
                        for f in rec["sources"])
-        lf = dict(kbuf=pf.kbuf or 48, persistent=bool(pf.flags & 2), tile_width=pf.tile_width or 8)
+        lf = dict(kbuf=fwd_keys(pf), persistent=bool(pf.flags & 2), tile_width=pf.tile_width or 8)
         if rec.get("kernel_sources_sha256") == hashlib.sha256(src).hexdigest() and rec.get("workload") == w["name"] \
                 and rec.get("hit_list") == base.hit_list and (dom == "bwd" or rec.get("launch_fwd") == lf):
             traffic = rec[f"render_{dom}_bytes"]
@@ -570,7 +577,7 @@ def main():
                    "step": "bvh+fwd+L1+bwd", "graph": not args.no_graph, "hit_list": base.hit_list,
                    "gradient": f"paper (eps2 {args.eps2:g})" if args.paper_gradient else "exact",
                    "loss": "mean L1" if args.loss == "l1" else "0.8 L2 + 0.2 D-SSIM (11x11, sigma 1.5)",
-                   "launch_fwd": dict(kbuf=pf.kbuf or 48, persistent=bool(pf.flags & 2),
+                   "launch_fwd": dict(kbuf=fwd_keys(pf), persistent=bool(pf.flags & 2),
                                       tile_width=pf.tile_width or 8),
                    "launch_bwd": dict(kbuf=pb.kbuf or 48, persistent=bool(pb.flags & 2),
                                       tile_width=pb.tile_width or 8)},

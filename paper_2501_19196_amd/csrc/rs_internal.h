@@ -43,8 +43,10 @@ inline int packet_shift(const rs_rays *rays, int64_t sets, const rs_params *p, i
 }
 // The same for a pass that neither writes nor reads stored lists (whose rows name lanes of the
 // packets that wrote them): where the Gaussians far outnumber the rays, even 16-ray packets are wide,
-// and 4-ray ones are faster (1M Gaussians, 320x180: 2.7 against 4.4 ms; 200k Gaussians, 400x300: 3.9
-// against 1.2).
+// and 4-ray ones are faster. Forward with 4-ray and 16-ray packets, by Gaussians per ray: 17 (1M, 320x180) 2.2 and 5.7 ms;
+// 5.2 (100k, 160x120) 0.99 and 1.48; 5.2 (300k, 320x180) 1.70 and 1.33; 4.1 (200k, 256x192) 0.83 and 0.95; 3.5 (200k,
+// 320x180) 0.71 and 1.00; 3.3 (100k, 200x150) 1.89 and 1.17; 2.0 (100k, 256x192) 1.76 and 0.96; 1.1 (100k, 360x260) 2.03
+// and 1.07. Random pixels are faster in 4-ray packets on either side (4.6: 10.0 and 13.7; 3.1: 5.2 and 7.8).
 inline int packet_shift_no_lists(const rs_rays *rays, int64_t sets, const rs_params *p, int64_t n_gauss)
 {
     const int ps = packet_shift(rays, sets, p, n_gauss);
