@@ -128,9 +128,10 @@ typedef struct {
  * hit_list: store-or-recompute choice of the adjoint (0..4096; 0 = recompute):
  * with C > 0 the forward also records the ids of the Gaussians each ray
  * composites, in a pool of C 4-byte slots per ray on average inside the ray
- * state (per compositing step of its wavefront a packet stores one
- * row: the ids of the lanes that took a hit at that step and their 64-bit lane
- * mask, in chunks of 8 slots per ray of a packet), and the adjoint replays those lists
+ * state (per compositing step of its wavefront a packet stores the ids of the
+ * lanes that took a hit at that step, and per row, one step of a 64-ray packet or up
+ * to four of a 16-ray one, two words of lane masks, in chunks of 8 slots per ray of a
+ * packet), and the adjoint replays those lists
  * instead of traversing the BVH again. The rays of a packet that finds the pool
  * exhausted are traversed again by the adjoint. The gradients are the same (up to
  * float atomic order). The mesh renders keep one pool for all their ray sets in

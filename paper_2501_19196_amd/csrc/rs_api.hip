@@ -546,7 +546,7 @@ static int lists_download(const rs_rays *rays, const rs_params *p, const int4 *d
             hipMemcpy(slots.data(), P.slots, size_t(used) * P.chunk_slots * 4, hipMemcpyDeviceToHost) != hipSuccess)
             return RS_ERR_HIP;
     }
-    // a packet's rows, first to last: (first slot, lane mask); a chunk's rows are found
+    // a packet's steps, first to last: (first slot, lane mask); a chunk's rows are found
     // from its fill backwards, each row ending with its mask
     std::unordered_map<int32_t, std::vector<std::pair<int64_t, uint64_t>>> chains;
     for (int64_t i = 0; i < m; ++i) {
@@ -569,7 +569,15 @@ static int lists_download(const rs_rays *rays, const rs_params *p, const int4 *d
                         const int32_t k = __builtin_popcountll(mask);
                         if (k + 2 > end) break;
                         end -= k + 2;
-                        rows.emplace_back(int64_t(c) * P.chunk_slots + end, mask);
+                        const int64_t first = int64_t(c) * P.chunk_slots + end;
+                        if (pkt_shift == 6) {
+                            rows.emplace_back(first, mask);
+                            continue;
+                        }
+                        for (int t = kRowSteps - 1; t >= 0; --t) {  // 16 lanes a step
+                            const uint64_t lanes = (mask >> (16 * t)) & 0xffffull;
+                            if (lanes) rows.emplace_back(first + __builtin_popcountll(mask & ((1ull << (16 * t)) - 1)), lanes);
+                        }
                     }
                 }
                 std::reverse(rows.begin(), rows.end());

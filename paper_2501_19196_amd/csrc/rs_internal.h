@@ -226,15 +226,20 @@ struct SetState {
 };
 
 // Stored hit lists: one pool shared by every packet of a launch. A packet's
-// wavefront appends one row per compositing step: the entries of the lanes that
+// wavefront appends, per compositing step, the entries of the lanes that
 // consumed a hit at that step, in lane order (the Gaussian index it composited,
 // or the index | kListSecond for a hit it only collected in the paper variant's
-// second phase), then the 64-bit mask of those lanes as two words. Rows are
-// packed into chunks of 4-byte slots (8 per ray of a packet; a row never straddles two
+// second phase). A row is one step of a 64-ray packet, or up to four of a 16-ray one,
+// and ends with 64 mask bits as two words: the lanes of its step, or 16 bits a step. With a row per step a
+// 16-ray packet's masks took a quarter of its slots, and pools that suffice for 64-ray packets ran out
+// (list adjoint of 96x96 rays with mirrors, 500,000 Gaussians, 64 slots a ray: 6.35 -> 0.75 ms; where the pool
+// sufficed, 16-ray packets' adjoint is 4 % faster, 0.347 -> 0.333 ms at 251x187 over 20,000).
+// Rows are packed into chunks of 4-byte slots (8 per ray of a packet; a row never straddles two
 // chunks), linked backwards per packet; fill[c] is the number of slots chunk c
 // holds. The pool header holds the chunk counter (64-bit) and a flag set when a
 // packet found the pool exhausted (its later rows are not stored).
 constexpr int kChunkSlots = 512;  // the unit in which pools are sized, and a chunk of 64-ray packets
+constexpr int kRowSteps = 4;      // steps in a row of a 16-ray packet
 inline int chunk_slots_of(int pkt_shift) { return kChunkSlots >> (6 - pkt_shift); }
 constexpr uint32_t kListIdle = 0xffffffffu;
 constexpr uint32_t kListSecond = 0x80000000u;
@@ -244,7 +249,7 @@ struct ListPool {
     int32_t *fill;            // [chunks] slots used
     uint32_t *slots;          // [chunks][chunk_slots]
     int64_t chunks;
-    int32_t chunk_slots;
+    int32_t chunk_slots;  // kChunkSlots: 64-ray packets, a row a step
 };
 inline int64_t list_chunks(int64_t slots_wanted)
 {

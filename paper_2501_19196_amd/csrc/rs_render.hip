@@ -788,32 +788,66 @@ struct ListCursor {
     bool ok;        // false once the pool was found exhausted
 };
 
-// Appends one row (called from wave-uniform control flow): the entries of the lanes
-// whose `entry` is not kListIdle, in lane order, then their lane mask as two words.
-// A row that does not fit the current chunk starts a new one, taken from the pool
-// and linked to the packet's previous chunk. Once the pool is exhausted the packet
-// stores nothing more (the adjoint then traverses for its rays, or, for the paper
-// variant, the sticky status reports it).
 // Ends a block that only some lanes run, before wave-uniform values meet again: without it the
 // compiler folds the block's end into the next join, takes that join's values for divergent and
 // keeps them, and every branch on them, per lane.
 __device__ inline void rejoin() { __builtin_amdgcn_wave_barrier(); }
 
-__device__ inline void list_append(const ListPool &pool, ListCursor &L, uint32_t entry, int lane, bool paper,
-                                   int32_t *status)
+// Ends a row whose steps took the lanes `mask`: its masks as two words.
+__device__ inline void list_end_row(const ListPool &pool, ListCursor &L, uint64_t mask, int lane)
+{
+    uint32_t *end = pool.slots + int64_t(L.chunk) * pool.chunk_slots + L.fill;
+    if (lane == 0) {
+        __builtin_nontemporal_store(uint32_t(mask), end);
+        __builtin_nontemporal_store(uint32_t(mask >> 32), end + 1);
+    }
+    rejoin();
+    L.fill += 2;
+    L.slots += 2;
+    ++L.rows;
+}
+
+// steps in a row of a 16-ray packet, from its masks
+__device__ inline int32_t row_steps(uint64_t mask) { return (79 - __builtin_clzll(mask)) >> 4; }
+
+// Whether a row is one step. ROWS: steps in a row, 0: the pool says (read at run time, it cost the frontier's 64-ray
+// packets 1.5 % with mirrors over 500,000 Gaussians, 22.1 against 21.8 ms a forward; known when compiled, 21.95).
+template <int ROWS>
+__device__ inline bool one_step(const ListPool &pool)
+{
+    return ROWS == 1 || (ROWS == 0 && pool.chunk_slots == kChunkSlots);
+}
+
+// Appends one step (called from wave-uniform control flow): the entries of the lanes whose `entry` is not
+// kListIdle, in lane order. The masks of the open row of a 16-ray packet wait in `open` (LDS: in registers
+// they would cost every packet). A row ends after kRowSteps steps, or where the next step and the masks
+// do not fit the current chunk: that one starts a new chunk, taken from the pool
+// and linked to the packet's previous chunk. Once the pool is exhausted the packet
+// stores nothing more (the adjoint then traverses for its rays, or, for the paper
+// variant, the sticky status reports it).
+template <int ROWS>
+__device__ inline void list_append(const ListPool &pool, ListCursor &L, uint64_t &open, uint32_t entry, int lane,
+                                   bool paper, int32_t *status)
 {
     const uint64_t m = wave_ballot(entry != kListIdle);
     if (m == 0) return;
-    const int32_t need = __popcll(m) + 2;
-    if (L.chunk < 0 || L.fill + need > pool.chunk_slots) {
+    const int32_t k = __popcll(m);
+    const bool wide = one_step<ROWS>(pool);
+    uint64_t mask = 0;
+    if (!wide)
+        mask = (uint64_t(uint32_t(__builtin_amdgcn_readfirstlane(int32_t(open >> 32)))) << 32) |
+               uint32_t(__builtin_amdgcn_readfirstlane(int32_t(open)));
+    if (L.chunk < 0 || L.fill + k + 2 > pool.chunk_slots) {
+        if (mask) list_end_row(pool, L, mask, lane);
+        mask = 0;
         int32_t c = L.spare, spare = -1;
         if (lane == 0) {
             if (L.chunk >= 0) pool.fill[L.chunk] = L.fill;
             if (c >= 0) {
                 spare = pool.prev[c];
             } else {
-                const unsigned long long k = atomicAdd(pool.hdr, 1ull);
-                c = k < (unsigned long long)pool.chunks ? int32_t(k) : -1;
+                const unsigned long long at = atomicAdd(pool.hdr, 1ull);
+                c = at < (unsigned long long)pool.chunks ? int32_t(at) : -1;
             }
         }
         rejoin();
@@ -840,19 +874,34 @@ __device__ inline void list_append(const ListPool &pool, ListCursor &L, uint32_t
         const uint32_t below = __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
         __builtin_nontemporal_store(entry, row + below);
     }
-    if (lane == 0) {
-        __builtin_nontemporal_store(uint32_t(m), row + need - 2);
-        __builtin_nontemporal_store(uint32_t(m >> 32), row + need - 1);
+    if (wide) {
+        if (lane == 0) {
+            __builtin_nontemporal_store(uint32_t(m), row + k);
+            __builtin_nontemporal_store(uint32_t(m >> 32), row + k + 1);
+        }
+        rejoin();
+        L.fill += k + 2;
+        L.slots += k + 2;
+        ++L.rows;
+        return;
     }
     rejoin();
-    L.fill += need;
-    L.slots += need;
-    ++L.rows;
+    L.fill += k;
+    L.slots += k;
+    const int32_t step = mask ? row_steps(mask) : 0;
+    mask |= m << (16 * step);
+    if (step + 1 == kRowSteps) {
+        list_end_row(pool, L, mask, lane);
+        mask = 0;
+    }
+    open = mask;  // every lane the same word
 }
 
-// Records the fill of the packet's last chunk (after its last row).
-__device__ inline void list_close(const ListPool &pool, const ListCursor &L, int lane)
+// Ends the packet's last row and records the fill of its last chunk.
+template <int ROWS>
+__device__ inline void list_close(const ListPool &pool, ListCursor &L, uint64_t open, int lane)
 {
+    if (!one_step<ROWS>(pool) && L.ok && L.chunk >= 0 && wave_ballot(open != 0)) list_end_row(pool, L, open, lane);
     if (L.ok && L.chunk >= 0 && lane == 0) pool.fill[L.chunk] = L.fill;
 }
 
@@ -1017,12 +1066,15 @@ struct LaneState {
 
 // What a lane seldom writes lives in LDS: T just before the composited hit that took T below the
 // normal floats (to 0, or into the subnormals, where T_{k+1} / (1 - alpha_k) would lose its digits)
-// and that hit's index, and how many composited ids were stored when the list pool ran out.
+// and that hit's index, and how many composited ids were stored when the list pool ran out. And the lane masks of
+// the open list row.
 struct LaneCold {
     float Tz[kWave];
     int32_t z[kWave], stored[kWave];
+    uint64_t open;
 };
 
+template <int ROWS>
 __device__ inline void lane_reset(LaneState &S, LaneCold &C, bool live, int lane)
 {
     S.A = Accum{1.0f, 0.0f, 0.0f, 0.0f, 0};
@@ -1033,11 +1085,12 @@ __device__ inline void lane_reset(LaneState &S, LaneCold &C, bool live, int lane
     S.extra = 0;
     C.Tz[lane] = 0.0f;
     C.z[lane] = -1;
+    if (ROWS != 1) C.open = 0;
 }
 
 // One compositing step of the wave: the lanes with `act` consume their hit `key`, of opacity al and
 // colour c.
-template <bool PAPER>
+template <bool PAPER, int ROWS>
 __device__ inline void consume_known(bool act, double key, float al, float cr, float cg, float cb, LaneState &S,
                                      LaneCold &C, const Ptrs &ptr, const RenderParams &P, bool lists, ListCursor &LC,
                                      int lane)
@@ -1077,7 +1130,7 @@ __device__ inline void consume_known(bool act, double key, float al, float cr, f
         rejoin();
     }
     if (lists && LC.ok) {
-        list_append(ptr.pool, LC, entry, lane, paper, ptr.status);
+        list_append<ROWS>(ptr.pool, LC, C.open, entry, lane, paper, ptr.status);
         if (!LC.ok) C.stored[lane] = S.A.n - (entry < kListSecond ? 1 : 0);
     }
     rejoin();
@@ -1085,7 +1138,7 @@ __device__ inline void consume_known(bool act, double key, float al, float cr, f
 
 // The same with the hit's opacity and colour fetched here (Gaussian at sorted position js): alpha is
 // recomputed from the record with the leaf test's own arithmetic.
-template <bool PAPER>
+template <bool PAPER, int ROWS>
 __device__ inline void consume(bool act, double key, int32_t js, LaneState &S, LaneCold &C,
                                const float4 *__restrict__ records, const Ptrs &ptr, const RenderParams &P, bool zc,
                                bool lists, ListCursor &LC, int lane)
@@ -1104,14 +1157,15 @@ __device__ inline void consume(bool act, double key, int32_t js, LaneState &S, L
         }
     }
     rejoin();
-    consume_known<PAPER>(act, key, al, cr, cg, cb, S, C, ptr, P, lists, LC, lane);
+    consume_known<PAPER, ROWS>(act, key, al, cr, cg, cb, S, C, ptr, P, lists, LC, lane);
 }
 
 // The outputs and the adjoint's starting state of a packet's rays.
+template <int ROWS>
 __device__ inline void write_rays(const LaneState &S, const LaneCold &C, const LaneRay &LR, const RaySet &R,
-                                  const Ptrs &ptr, const ListCursor &LC, bool lists, int lane)
+                                  const Ptrs &ptr, ListCursor &LC, bool lists, int lane)
 {
-    if (lists) list_close(ptr.pool, LC, lane);
+    if (lists) list_close<ROWS>(ptr.pool, LC, C.open, lane);
     if (!LR.valid) return;
     const float orr = __builtin_fmaf(S.A.T, LR.bgr, S.A.Cr), og = __builtin_fmaf(S.A.T, LR.bgg, S.A.Cg),
                 ob = __builtin_fmaf(S.A.T, LR.bgb, S.A.Cb);
@@ -1149,7 +1203,7 @@ __device__ inline void add_counts(const FwdCount &c, const Ptrs &ptr, int lane)
 
 // The depth-first walk of a packet, in rounds, until no lane is live. Returns false when the traversal
 // stack overflowed.
-template <typename BUF, bool BRUTE, bool COUNT, bool PAPER>
+template <typename BUF, bool BRUTE, bool COUNT, bool PAPER, int ROWS>
 __device__ inline bool walk_rounds(LaneState &S, LaneCold &C, const LaneRay &LR, bool zc, bool lists, ListCursor &LC,
                                    const float4 *__restrict__ records, const float4 *__restrict__ nodes,
                                    const int32_t *__restrict__ gidx, const int32_t *__restrict__ inv, const Ptrs &ptr,
@@ -1235,7 +1289,7 @@ __device__ inline bool walk_rounds(LaneState &S, LaneCold &C, const LaneRay &LR,
             more = act_mask != 0;
             if (!more) break;
             if (COUNT) cnt.lcomp += __popcll(act_mask);
-            consume<PAPER>(act, key_s, js_s, S, C, records, ptr, P, zc, lists, LC, lane);
+            consume<PAPER, ROWS>(act, key_s, js_s, S, C, records, ptr, P, zc, lists, LC, lane);
         }
         // a lane whose buffer did not fill has consumed all its hits
         if (live && round_last == kNoHit) live = false;
@@ -1272,17 +1326,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(waves_for(K,
         __shared__ LaneCold cold;
         LaneState S;
         S.ray = LR.ray;
-        lane_reset(S, cold, LR.valid && P.n_gauss > 0 && LR.tmax > P.t_min, lane);
+        lane_reset<0>(S, cold, LR.valid && P.n_gauss > 0 && LR.tmax > P.t_min, lane);
         typename FwdBuf<K>::type hb;
         if constexpr (!std::is_same<typename FwdBuf<K>::type, HitBuf<K>>::value) {
             __shared__ double ring[kTailKeys * kWave];
             hb.ring = ring;
             hb.lane = lane;
         }
-        if (!walk_rounds<typename FwdBuf<K>::type, BRUTE, COUNT, true>(S, cold, LR, zc, lists, LC, records, nodes, gidx, inv, ptr,
+        if (!walk_rounds<typename FwdBuf<K>::type, BRUTE, COUNT, true, 0>(S, cold, LR, zc, lists, LC, records, nodes, gidx, inv, ptr,
                                                                        P, hb, lane, cnt))
             if (lane == 0) atomicOr(ptr.status, kStatusStack);
-        write_rays(S, cold, LR, R, ptr, LC, lists, lane);
+        write_rays<0>(S, cold, LR, R, ptr, LC, lists, lane);
         if (COUNT) {
             cnt.rows += uint64_t(LC.rows);
             cnt.slots += uint64_t(LC.slots);
@@ -1551,7 +1605,8 @@ __device__ inline double no_hit_here()
     return __longlong_as_double((long long)((uint64_t(hi) << 32) | lo));
 }
 
-template <int K, bool COUNT>
+// ROWS: steps in a row of its stored lists (see list_append).
+template <int K, bool COUNT, int ROWS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFrontWaves))) void k_render_front(
     const float4 *__restrict__ records, const float4 *__restrict__ nodes, const int32_t *__restrict__ gidx,
     const int32_t *__restrict__ inv, const Ptrs ptr, const RenderParams P)
@@ -1574,7 +1629,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFrontWaves)
             const LaneRay LR = lane_ray(P, ptr, pkt, lane);
             S.ray = LR.ray;
             const bool wanted = LR.valid && P.n_gauss > 0 && LR.tmax > P.t_min;
-            lane_reset(S, cold, wanted, lane);
+            lane_reset<ROWS>(S, cold, wanted, lane);
             zc = ptr.set[LR.si].zero_colour != 0;
             lists = P.lists && ptr.set[LR.si].list != nullptr;
             // hits are taken with start < key < stop
@@ -1937,7 +1992,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFrontWaves)
                                 rejoin();
                                 key = hb.front();
                                 js = inv[key != kNoHit ? hit_key_gid(key) : 0u];
-                                consume<false>(act, key_s, js_s, S, cold, records, ptr, P, zc, lists, LC, lane);
+                                consume<false, ROWS>(act, key_s, js_s, S, cold, records, ptr, P, zc, lists, LC, lane);
                             }
                             on_mask = grp & wave_ballot(S.live);
                             if (end || !on_mask) break;
@@ -2026,7 +2081,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFrontWaves)
         }
         const LaneRay LR = lane_ray(P, ptr, pkt, lane);
         if (redo) {
-            lane_reset(S, cold, LR.valid && P.n_gauss > 0 && LR.tmax > P.t_min, lane);
+            lane_reset<ROWS>(S, cold, LR.valid && P.n_gauss > 0 && LR.tmax > P.t_min, lane);
             LC = ListCursor{0, -1, 0, 0, LC.chunk, true};
         }
         if (wave_ballot(S.live)) {
@@ -2037,12 +2092,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kFrontWaves)
             wb.ring = reinterpret_cast<double *>(&F);
             wb.lane = lane;
             __syncthreads();
-            if (!walk_rounds<Buf, false, COUNT, false>(S, cold, LR, zc, lists, LC, records, nodes, gidx, inv, ptr, P, wb, lane,
+            if (!walk_rounds<Buf, false, COUNT, false, ROWS>(S, cold, LR, zc, lists, LC, records, nodes, gidx, inv, ptr, P, wb, lane,
                                                        cnt))
                 if (lane == 0) atomicOr(ptr.status, kStatusStack);
             __syncthreads();
         }
-        write_rays(S, cold, LR, ptr.set[LR.si], ptr, LC, lists, lane);
+        write_rays<ROWS>(S, cold, LR, ptr.set[LR.si], ptr, LC, lists, lane);
         if (COUNT) {
             cnt.rows += uint64_t(LC.rows);
             cnt.slots += uint64_t(LC.slots);
@@ -2225,26 +2280,41 @@ __device__ inline void row_seek(const int32_t *__restrict__ prev, const int32_t 
     }
 }
 
-// Reads the row ending at `start` of `chunk` (its lane mask), moves `start` to the row's first
-// slot, and returns this lane's entry (kListIdle for a lane without one, or not live).
-__device__ inline uint32_t row_entry(const uint32_t *__restrict__ slots, int32_t chunk_slots, int32_t chunk,
-                                     int32_t &start, bool live, int lane)
+// Where the list adjoint stands: the row read last begins at slot `start` of `chunk`, `step` of its steps are left.
+struct RowCursor {
+    int32_t chunk, start, step;
+    uint64_t mask;
+};
+
+// Moves to the step before, and returns whether there is one; `entry` is this lane's (kListIdle for a
+// lane without one, or not live).
+template <int ROWS>
+__device__ inline bool step_back(const ListPool &pool, const int32_t *__restrict__ prev, const int32_t *__restrict__ fill,
+                                 const uint32_t *__restrict__ slots, RowCursor &c, bool live, int lane, uint32_t &entry)
 {
-    const uint32_t *row_end = slots + int64_t(chunk) * chunk_slots + start;
-    // the mask's address is wave-uniform: read it through the constant address space, so it is
-    // a scalar load (the pool is only read by this kernel)
-    typedef const __attribute__((address_space(4))) uint32_t *const_u32;
-    const const_u32 mend = (const_u32)(row_end - 2);
-    const uint64_t m = uint64_t(mend[0]) | (uint64_t(mend[1]) << 32);
-    const int32_t k = __popcll(m);
-    start -= k + 2;
+    entry = kListIdle;
+    if (ROWS == 1 || c.step == 0) {
+        row_seek(prev, fill, c.chunk, c.start);
+        if (c.chunk < 0) return false;
+        // the masks' address is wave-uniform: read it through the constant address space, so it is
+        // a scalar load (the pool is only read by this kernel)
+        typedef const __attribute__((address_space(4))) uint32_t *const_u32;
+        const const_u32 mend = (const_u32)(slots + int64_t(c.chunk) * pool.chunk_slots + c.start - 2);
+        c.mask = uint64_t(mend[0]) | (uint64_t(mend[1]) << 32);
+        c.start -= __popcll(c.mask) + 2;
+        c.step = ROWS == 1 ? 1 : row_steps(c.mask);
+    }
+    --c.step;
+    const int sh = 16 * c.step;  // 0 where a row is one step
+    const uint64_t m = c.mask >> sh;  // bits of later steps lie above the packet's lanes
+    const uint32_t *row = slots + int64_t(c.chunk) * pool.chunk_slots + c.start + __popcll(c.mask & ((1ull << sh) - 1));
     const bool mine = ((m >> lane) & 1ull) != 0;
     const uint32_t below = __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
-    const uint32_t *row = row_end - 2 - k;
-    return live && mine ? row[below] : kListIdle;
+    if (live && mine) entry = row[below];
+    return true;
 }
 
-template <bool COUNT>
+template <bool COUNT, int ROWS>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kListWaves))) void k_adjoint_list(
     const float4 *__restrict__ records, const int32_t *__restrict__ inv, const Ptrs ptr, const RenderParams P)
 {
@@ -2279,16 +2349,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kListWaves))
         // the packet's last chunk (lane 0 always holds one of the packet's rays)
         int32_t chunk = __builtin_amdgcn_readfirstlane(li.z);
         if (!wave_ballot(live) || chunk < 0) continue;
-        // Rows are walked from the last to the first: a row ends with its lane mask, so the
-        // mask at the row's end gives its start, which is the previous row's end. While a row is
+        // Rows are walked from the last to the first: a row ends with its lane masks, so the
+        // masks at the row's end give its start, which is the previous row's end. While a step is
         // processed, the next one's sorted positions and the one after that's entries are loaded, so
-        // a row waits for its records alone.
-        int32_t start = fill[chunk];
-        row_seek(prev, fill, chunk, start);
-        uint32_t e1 = kListIdle, e0 = kListIdle;
+        // a step waits for its records alone.
+        RowCursor rc{chunk, fill[chunk], 0, 0};
+        uint32_t e1, e0 = kListIdle;
         int32_t js0 = 0;
-        bool row1 = chunk >= 0, row0 = true;
-        if (row1) e1 = row_entry(slots, ptr.pool.chunk_slots, chunk, start, live, lane);
+        bool row1 = step_back<ROWS>(ptr.pool, prev, fill, slots, rc, live, lane, e1), row0 = true;
         while (row0) {
             const uint32_t cur = e0;
             const int32_t js = js0;
@@ -2296,11 +2364,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(kListWaves))
             row0 = row1;
             js0 = inv[e0 != kListIdle ? e0 & ~kListSecond : 0u];  // idle lanes read Gaussian 0 (unused)
             e1 = kListIdle;
-            if (row1) {
-                row_seek(prev, fill, chunk, start);
-                row1 = chunk >= 0;
-                if (row1) e1 = row_entry(slots, ptr.pool.chunk_slots, chunk, start, live, lane);
-            }
+            if (row1) row1 = step_back<ROWS>(ptr.pool, prev, fill, slots, rc, live, lane, e1);
             const bool act = cur != kListIdle;
             if (!wave_ballot(act)) continue;
             const bool comp = act && cur < kListSecond;
@@ -2416,13 +2480,30 @@ static int plain_grid(int64_t n_packets)
     return int((n_packets + deal - 1) / deal * deal);
 }
 
-template <int K>
+template <int ROWS>
+static void launch_adjoint_list(const KernArgs &a, const Ptrs &ptr, const RenderParams &P, hipStream_t st)
+{
+    if (P.count)
+        k_adjoint_list<true, ROWS><<<a.grid, kWave, 0, st>>>(a.records, a.inv, ptr, P);
+    else
+        k_adjoint_list<false, ROWS><<<a.grid, kWave, 0, st>>>(a.records, a.inv, ptr, P);
+}
+
+template <int K, int ROWS>
 static void launch_front(const KernArgs &a, const Ptrs &ptr, const RenderParams &P, hipStream_t st)
 {
     if (P.count)
-        k_render_front<K, true><<<a.grid, kWave, 0, st>>>(a.records, a.nodes, a.gidx, a.inv, ptr, P);
+        k_render_front<K, true, ROWS><<<a.grid, kWave, 0, st>>>(a.records, a.nodes, a.gidx, a.inv, ptr, P);
     else
-        k_render_front<K, false><<<a.grid, kWave, 0, st>>>(a.records, a.nodes, a.gidx, a.inv, ptr, P);
+        k_render_front<K, false, ROWS><<<a.grid, kWave, 0, st>>>(a.records, a.nodes, a.gidx, a.inv, ptr, P);
+}
+template <int K>
+static void launch_front(const KernArgs &a, const Ptrs &ptr, const RenderParams &P, hipStream_t st)
+{
+    if (P.lists && ptr.pool.chunk_slots != kChunkSlots)
+        launch_front<K, kRowSteps>(a, ptr, P, st);
+    else
+        launch_front<K, 1>(a, ptr, P, st);
 }
 
 template <int K>
@@ -2549,10 +2630,10 @@ int launch_sets(const BvhDesc &D, const rs_gaussians *g, const rs_params *p, int
         // the hit-buffer size never changes the result (same hits, same order, same arithmetic);
         // the default is the fastest measured size on MI355X
         if (pass == Pass::AdjointList) {
-            if (P.count)
-                k_adjoint_list<true><<<a.grid, kWave, 0, st>>>(a.records, a.inv, ptr, P);
+            if (ptr.pool.chunk_slots != kChunkSlots)
+                launch_adjoint_list<kRowSteps>(a, ptr, P, st);
             else
-                k_adjoint_list<false><<<a.grid, kWave, 0, st>>>(a.records, a.inv, ptr, P);
+                launch_adjoint_list<1>(a, ptr, P, st);
         } else if (P.front) {
             switch (kbuf) {
             case 16: launch_front<16>(a, ptr, P, st); break;

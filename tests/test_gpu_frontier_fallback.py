@@ -144,3 +144,57 @@ def test_secondary_sets_give_way_after_two_rounds():
     assert c["packets"] == cw["packets"] == 3 * 24 * 24
     assert c["rounds"] <= cw["rounds"] + c["packets"]
     assert c["leaf_visits"] <= 1.25 * cw["leaf_visits"]
+
+
+@pytest.mark.parametrize("w,h,views", [(96, 96, True), (97, 61, True), (1000, 1, False), (5, 3, True)])
+def test_rows_of_small_packets_hold_four_steps(w, h, views):
+    """A 16-ray packet ends a row after four steps (or a chunk), so its masks take few of its slots; the lists and
+    the gradients are those of the traversal."""
+    print("case four steps a row", w, h, flush=True)
+    G, R = _g()
+    sc = scenes.scene_config2(seed=99, n=20000)
+    o, d = pinhole_rays(look_at_camera((0, 0, -4), (0, 0, 0), (0, 1, 0), w, h, fov_y_deg=35))
+    vs = [(0, w, h)] if views else None
+    p = R.Params(hit_list=512, flags=8)
+    out, st, s, (bvh, g, rays) = G.render(sc, o, d, p, views=vs)
+    c = R.read_counters(bvh)
+    print(c, flush=True)
+    assert s == 0
+    assert c["list_slots"] == c["lane_composited"] + 2 * c["list_rows"]
+    # a step has at least one hit; a row ends after four steps, or where a 128-slot chunk or the packet does
+    assert c["list_rows"] <= c["lane_composited"] / 4 + c["list_slots"] / (128 - 16 - 2) + c["packets"]
+    pw = R.Params(hit_list=512, stack_depth=64)
+    ref, st0, s0, _ = G.render(sc, o, d, pw, views=vs, bvh=bvh, g=g)
+    assert s0 == 0
+    np.testing.assert_array_equal(out, ref)
+    _same_lists(R, rays, p, st, pw, st0, 512)
+    rng = np.random.default_rng(99)
+    grad = G.dev(np.float32(rng.normal(size=(o.shape[0], 3))))
+    a = R.render_bwd(bvh, g, rays, p, grad, st)
+    p0 = R.Params()
+    _, st1, _, _ = G.render(sc, o, d, p0, views=vs, bvh=bvh, g=g)
+    b = R.render_bwd(bvh, g, rays, p0, grad, st1)
+    for x, y in zip(a, b):  # sums of the same contributions in another order
+        assert float((x - y).double().norm()) <= 1e-4 * float(y.double().norm())
+
+
+def test_a_pool_of_the_mean_length_suffices_in_small_packets():
+    """Mirror and shadow sets at 96x96, lists of 47 on average, a pool of 64 slots a ray: the lists are complete, as
+    they are in 64-ray packets."""
+    print("case pool reach", flush=True)
+    G, R = _g()
+    sc = scenes.scene_config4(seed=98, n=500000)
+    o, d = pinhole_rays(look_at_camera((4.2, 4.2, 3), (0, 0, 0.5), (0, 0, 1), 96, 96))
+    quad = np.float32([[-3, -3, 0], [3, -3, 0], [3, 3, 0], [-3, 3, 0]])
+    mesh = R.Mesh(G.dev(quad), G.dev(np.int32([[0, 1, 2], [0, 2, 3]])), G.dev(np.int32([1, 1])))
+    mbvh, sh, g, rays = R.build_mesh_bvh(mesh), R.Shading(), G.gaussians(sc), G.rays_of(o, d, [(0, 96, 96)])
+    big = R.Params(hit_list=256)
+    bvh = R.build_bvh(g, big)
+    _, frame = R.render_mesh_fwd(bvh, mbvh, g, mesh, sh, rays, big)
+    mean = sum(R.mesh_hit_lists(rays, big, sh, frame, k, cap=1)["count"].mean() for k in range(3)) / 3
+    p = R.Params(hit_list=int(np.ceil(1.2 * mean)) + 4)
+    print("mean list", mean, "slots", p.hit_list, flush=True)
+    _, frame = R.render_mesh_fwd(bvh, mbvh, g, mesh, sh, rays, p)
+    for k in range(3):
+        lists = R.mesh_hit_lists(rays, p, sh, frame, k, cap=1)
+        np.testing.assert_array_equal(lists["stored"], lists["count"])
